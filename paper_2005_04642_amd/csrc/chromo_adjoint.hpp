@@ -205,10 +205,6 @@ __device__ __forceinline__ void solid_tap_weights_r(int r, const unsigned char* 
   }
 }
 
-struct Radii {
-  int g, k, p, u;
-};
-
 // ---------------------------------------------------------------------------
 // pass 1: local adjoint of correction tensor, relaxation, reconstruction and
 // recolour at one site.  Inputs: pre-collision totals f_i, colour densities,

@@ -53,14 +53,7 @@ constexpr double WHOLE_BUFFER_LIMIT = 4294967296.0;
 
 int halo(const lbm_params& p) { return p.stencil[0] + p.stencil[1] + p.stencil[3]; }
 
-// Stencil profiles with instantiations of the step kernel's mask variant, the
-// walled batch kernel and the masked adjoint: (3,3,3,3), the "fast" (3,1,3,1)
-// and the "compact" (1,1,1,1).
-bool special_profile(const int* r) {
-  return (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3) || (r[0] == 3 && r[1] == 1 && r[2] == 3 && r[3] == 1) ||
-         (r[0] == 1 && r[1] == 1 && r[2] == 1 && r[3] == 1);
-}
-
+using chromo::special_profile;
 using chromo::MASS_BLOCKS;
 
 const chromo::Ops* ops_of(int storage) {
@@ -119,32 +112,83 @@ int validate(const lbm_params* p) {
   return LBM_OK;
 }
 
+chromo::Geom geom_of(const lbm_params& p) {
+  chromo::Geom g = {};
+  g.nx = p.nx;
+  g.ny = p.ny;
+  g.walls = p.walls_y;
+  g.F = p.walls_y ? p.ny - 2 : p.ny;
+  g.plane = p.nx * p.ny;
+  return g;
+}
+
+void cut_rows(chromo::Geom& g, int nch) {
+  g.TY = (g.F + nch - 1) / nch;
+  g.nchunks = (g.F + g.TY - 1) / g.TY;
+}
+
+void cut_columns(chromo::Geom& g, int txmax) {
+  g.nstrips = (g.nx + txmax - 1) / txmax;
+  g.TX = (g.nx + g.nstrips - 1) / g.nstrips;
+}
+
 // Strips of at most NTX-2H columns; chunks of rows such that all tiles run in
 // a single wave of workgroups (one workgroup fills a CU: its LDS rings take
 // nearly all of the CU's LDS), i.e. nstrips * nchunks <= number of CUs, with
 // chunks no shorter than one march iteration (4 rows).  A chunk's march
 // starts with a fixed pipeline fill, so on small lattices the time per step is
 // the fill plus a few iterations whatever the chunk height: there, more and
-// shorter chunks (down to 4 rows) run faster (512^2 FP32: 40 -> 24 us per step
-// against a 24-row minimum), while large lattices are bound by the CU count.
-chromo::Geom plan(const lbm_params& p, int ncu, int ntx) {
-  chromo::Geom g;
-  g.nx = p.nx;
-  g.ny = p.ny;
-  g.walls = p.walls_y;
-  g.F = p.walls_y ? p.ny - 2 : p.ny;
-  g.plane = p.nx * p.ny;
-  const int txmax = ntx - 2 * halo(p);
-  g.nstrips = (p.nx + txmax - 1) / txmax;
-  g.TX = (p.nx + g.nstrips - 1) / g.nstrips;
-  int nch = ncu / g.nstrips;
-  if (nch < 1) nch = 1;
-  int maxchunks = g.F / 4;
-  if (maxchunks < 1) maxchunks = 1;
-  if (nch > maxchunks) nch = maxchunks;
-  g.TY = (g.F + nch - 1) / nch;
-  g.nchunks = (g.F + g.TY - 1) / g.TY;
+// shorter chunks (down to 4 rows) run faster, while large lattices are bound
+// by the CU count.
+chromo::Geom plan_march(const lbm_params& p, int ncu, int ntx) {
+  chromo::Geom g = geom_of(p);
+  cut_columns(g, ntx - 2 * halo(p));
+  cut_rows(g, std::max(1, std::min(ncu / g.nstrips, g.F / 4)));
   return g;
+}
+
+// Tiles of 64 - 2H columns and at most TILE_WAVES * slots - 2H rows, one
+// workgroup per CU at a time: as many equal chunks as fill the rounds of
+// workgroups that the tallest tiles need, none below 4 rows (64^2 FP32: 6.8 us
+// per step at 4 rows, 8.3 at 14, 6.7 at 2).
+chromo::Geom plan_tile(const lbm_params& p, int ncu, int slots, int* rounds) {
+  chromo::Geom g = geom_of(p);
+  g.tile = slots;
+  cut_columns(g, 64 - 2 * halo(p));
+  const int tymax = chromo::TILE_WAVES * slots - 2 * halo(p);
+  const int minch = (g.F + tymax - 1) / tymax;
+  *rounds = (int)(((long long)g.nstrips * minch + ncu - 1) / ncu);
+  const int fill = (int)((long long)*rounds * ncu / g.nstrips);
+  cut_rows(g, std::max(minch, std::min(fill, g.F / 4)));
+  return g;
+}
+
+// Launch plan of the step and the fields: tiles (chromo_tile.hpp) for lattices
+// of a few rounds of workgroups, the march (chromo_kernels.hpp) above.  A tile
+// has no pipeline to fill but gathers more halo rows, which costs more than
+// the fill once the march's chunks are tall.  Measured per step on 256 CUs,
+// march against tile, periodic lattices: FP32 64^2 16.0 / 6.8 us, 256^2
+// 18.0 / 8.5, 512^2 22.1 / 14.5, 724^2 (2 rounds) 30.4 / 26.7, 900^2 (3)
+// 37.6 / 40.3; FP16 724^2 (2) 27.4 / 21.9, 900^2 (3) 34.4 / 32.4, 1024^2 (4)
+// 38.0 / 41.2; FP64 64^2 15.9 / 10.5, 512^2 (2) 39.3 / 29.4, 724^2 (4)
+// 58.7 / 57.3, 900^2 (6) 84.0 / 85.9.  Two region rows per wave where one
+// round of the shorter tiles holds the lattice (64^2 FP32: 6.8 us against 8.0
+// with three), else three (512^2: 14.5 against 16.8); FP64 has registers for two.
+chromo::Geom plan(const lbm_params& p, int ncu) {
+  int rounds = 0;
+  chromo::Geom g = plan_tile(p, ncu, 2, &rounds);
+  if (p.storage == LBM_STORAGE_F64) {
+    if (rounds <= 4) return g;
+  } else {
+    if (rounds == 1) return g;
+    g = plan_tile(p, ncu, 3, &rounds);
+    if (rounds <= (p.storage == LBM_STORAGE_F32 ? 2 : 3)) return g;
+  }
+  return plan_march(p, ncu, chromo::ntx_for(p.storage));
+}
+
+chromo::Geom plan_adjoint(const lbm_params& p, int ncu) {
+  return plan_march(p, ncu, chromo::ntx_for(p.storage, true));
 }
 
 // ---------------------------------------------------------------------------
@@ -283,8 +327,8 @@ int lbm_init(const lbm_params* p, const void* rhoN0, const void* force, void* po
   h->ws_bytes = ws_bytes;
   h->force = force;
   h->steps = 0;
-  h->g = plan(*p, ncu > 0 ? ncu : 1, chromo::ntx_for(p->storage));
-  h->g_adj = plan(*p, ncu > 0 ? ncu : 1, chromo::ntx_for(p->storage, true));
+  h->g = plan(*p, ncu > 0 ? ncu : 1);
+  h->g_adj = plan_adjoint(*p, ncu > 0 ? ncu : 1);
   h->ops = ops_of(p->storage);
   h->scratch = scr;
 
@@ -307,8 +351,8 @@ int lbm_set_cu_budget(lbm_handle* h, int32_t ncu_step, int32_t ncu_adjoint) {
   if (ncu < 1) ncu = 1;
   const int bs = ncu_step > 0 ? std::min(ncu_step, ncu) : ncu;
   const int ba = ncu_adjoint > 0 ? std::min(ncu_adjoint, ncu) : ncu;
-  h->g = plan(h->p, bs, chromo::ntx_for(h->p.storage));
-  h->g_adj = plan(h->p, ba, chromo::ntx_for(h->p.storage, true));
+  h->g = plan(h->p, bs);
+  h->g_adj = plan_adjoint(h->p, ba);
   return LBM_OK;
 }
 
@@ -581,19 +625,9 @@ int batch_validate(const lbm_params* p, int nsim) {
 
 // Tile plan of one lattice for workgroup width ntx and chunk height cap.
 chromo::Geom batch_geom(const lbm_params& p, int ntx, int tycap) {
-  chromo::Geom g;
-  g.nx = p.nx;
-  g.ny = p.ny;
-  g.walls = p.walls_y;
-  g.F = p.walls_y ? p.ny - 2 : p.ny;
-  g.plane = p.nx * p.ny;
-  const int txmax = ntx - 2 * halo(p);
-  g.nstrips = (p.nx + txmax - 1) / txmax;
-  g.TX = (p.nx + g.nstrips - 1) / g.nstrips;
-  int nch = (g.F + tycap - 1) / tycap;
-  if (nch < 1) nch = 1;
-  g.TY = (g.F + nch - 1) / nch;
-  g.nchunks = (g.F + g.TY - 1) / g.TY;
+  chromo::Geom g = geom_of(p);
+  cut_columns(g, ntx - 2 * halo(p));
+  cut_rows(g, std::max(1, (g.F + tycap - 1) / tycap));
   return g;
 }
 
@@ -830,8 +864,8 @@ int lbm_batch_init(const lbm_params* p, int nsim, const void* const* rhoN0, void
     h.ws_bytes = (size_t)(MASS_BLOCKS + 1) * 2 * sizeof(double);
     h.force = nullptr;
     h.steps = 0;
-    h.g = plan(p[k], ncu, chromo::ntx_for(p[k].storage));
-    h.g_adj = plan(p[k], ncu, chromo::ntx_for(p[k].storage, true));
+    h.g = plan(p[k], ncu);
+    h.g_adj = plan_adjoint(p[k], ncu);
     h.ops = b->ops;
     hipError_t e = b->ops->init(p[k], h.g, rhoN0[k], h.pops[0], stream);
     if (e != hipSuccess) {

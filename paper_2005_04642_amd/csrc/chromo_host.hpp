@@ -24,6 +24,17 @@ constexpr int NR_F64 = 4;
 // and backward values of a site at once: 512 threads leave 256 VGPRs.
 constexpr int NTX_ADJ_F32 = 128;
 
+// Waves of a tile kernel workgroup (Geom::tile gives the region rows per wave).
+constexpr int TILE_WAVES = 16;
+
+// Stencil profiles with instantiations of the step kernel's mask variant, the
+// walled batch kernel and the masked adjoint: (3,3,3,3), the "fast" (3,1,3,1)
+// and the "compact" (1,1,1,1).
+inline bool special_profile(const int* r) {
+  return (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3) || (r[0] == 3 && r[1] == 1 && r[2] == 3 && r[3] == 1) ||
+         (r[0] == 1 && r[1] == 1 && r[2] == 1 && r[3] == 1);
+}
+
 inline int ntx_for(int storage, bool adjoint = false) {
   return storage == LBM_STORAGE_F64 ? NTX_F64 : (adjoint ? NTX_ADJ_F32 : NTX_F32);
 }

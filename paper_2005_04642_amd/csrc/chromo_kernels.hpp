@@ -71,6 +71,7 @@ struct Geom {
   int nx, ny, walls, F;    // F = fluid rows: ny, or ny - 2 with walls
   int TX, nstrips, TY, nchunks;
   int plane;               // nx * ny
+  int tile;                // 0: the march; else the tile kernel (chromo_tile.hpp) with this many region rows per wave
   // set per storage format and workgroup shape at launch:
   unsigned pb, rb;         // byte strides of the storage words: word q of row y at q pb + y rb
   int period;              // period of the virtual row index: ny, or 2 F with walls
@@ -99,6 +100,11 @@ struct StepArgs {
   const unsigned char* bnc;
   Geom g;
   Coef<T> c;
+};
+
+// Radii of the four derivatives (grad rho^N, div m, grad Phi', div u).
+struct Radii {
+  int g, k, p, u;
 };
 
 // Launch modes of the step kernel: advance one step, write the macroscopic
@@ -450,10 +456,15 @@ struct RowTrack {
   __device__ __forceinline__ bool refl(const Geom& g) const { return WALLS && t >= g.F; }
 };
 
+// ring row of row index r; RING = 0: a plain array of rows, no wrap
 template <int RING>
 __device__ __forceinline__ int ring_row(int r) {
-  r %= RING;
-  return r < 0 ? r + RING : r;
+  if constexpr (RING == 0) {
+    return r;
+  } else {
+    r %= RING;
+    return r < 0 ? r + RING : r;
+  }
 }
 
 // App. B first-derivative stencil coefficients b_N (radius 1: 3; radius 3:
@@ -628,6 +639,55 @@ __device__ __forceinline__ float rsqrt_pos(float x) {
   return r * __builtin_fmaf(-0.5f * x * r, r, 1.5f);
 }
 __device__ __forceinline__ double rsqrt_pos(double x) { return 1.0 / sqrt(x); }
+
+// Colour densities of one site.
+template <typename T>
+__device__ __forceinline__ T density(const T* p) {
+  return ((p[0] + p[2]) + (p[4] + p[6])) + ((p[1] + p[3]) + (p[5] + p[7])) + p[8];
+}
+
+// Phi' (App. A); a solid site (MASK: no mass) holds the stencils' NaN marker.
+template <bool MASK, typename T>
+__device__ __forceinline__ T phi_prime(const Coef<T>& c, T rR, T rB) {
+  const T rho = rR + rB;
+  T phi = c.c06R * rR + c.phiB * rB - rho * T(1.0 / 3.0);
+  if (MASK && rho == T(0)) phi = __builtin_nan("");
+  return phi;
+}
+
+// Director m = grad rho^N / sqrt(|grad rho^N|^2 + eps^2).  MASK: a solid site
+// (rho^N = 0/0) marks m as well: its stencil sums mix fluid taps and are
+// finite when the site has fluid all round.
+template <bool MASK, typename T>
+__device__ __forceinline__ void director(const Coef<T>& c, T gx, T gy, T rhoN, T& mx, T& my) {
+  const T is = rsqrt_pos(gx * gx + gy * gy + c.eps2);
+  mx = gx * is;
+  my = gy * is;
+  if (MASK) {
+    if (!(rhoN == rhoN)) mx = my = __builtin_nan("");
+  }
+}
+
+// Interface force G = sigma K grad(rho^N)/2 + body force, and Guo's velocity
+// u = (j + G/2)/rho.  refl: a mirror row beyond a wall, whose y-components
+// change sign.  MASK: NaN marker at a solid site (1/0 need not give NaN).
+template <bool MASK, typename T>
+__device__ __forceinline__ void force_velocity(const Coef<T>& c, T K, T gnx, T gny, bool has_force, T fx, T fy,
+                                               bool refl, const T* f, T rho, T& Gx, T& Gy, T& ir, T& ux, T& uy) {
+  Gx = c.half_sigma * K * gnx + c.gx;
+  Gy = c.half_sigma * K * gny + (refl ? -c.gy : c.gy);
+  if (has_force) {
+    Gx += fx;
+    Gy += refl ? -fy : fy;
+  }
+  T jx, jy;
+  momenta(f, jx, jy);
+  if (refl) jy = -jy;
+  ir = recip(rho);
+  ux = (jx + T(0.5) * Gx) * ir;
+  uy = (jy + T(0.5) * Gy) * ir;
+  if (MASK && rho == T(0)) ux = uy = __builtin_nan("");
+}
 
 // Collision, recolour and store of one site (band O).
 // MASK: a site without mass (a solid site, whose words encode zero populations)
@@ -815,8 +875,7 @@ __device__ __forceinline__ void march_iter(int it, const StepArgs<T>& a, const v
     T* rf = st.rf[sM];
     T pr[9], pb[9];
     decode<ST>(st.pw, c, pr, pb, rf);
-    T rR = ((pr[0] + pr[2]) + (pr[4] + pr[6])) + ((pr[1] + pr[3]) + (pr[5] + pr[7])) + pr[8];
-    T rB = ((pb[0] + pb[2]) + (pb[4] + pb[6])) + ((pb[1] + pb[3]) + (pb[5] + pb[7])) + pb[8];
+    const T rR = density(pr), rB = density(pb);
     const int rm = ring_row<RING>(rowM);
     sm.at(F_RR, rm, tx) = rR;
     sm.at(F_RB, rm, tx) = rB;
@@ -856,15 +915,9 @@ __device__ __forceinline__ void march_iter(int it, const StepArgs<T>& a, const v
   if (it >= PP::ITN && tx >= RG && tx < NTX - RG) {
     T gx, gy;
     ring_grad<RG, RING, SM::STRIDE, SM::CS, T, MASK>(sm.field(F_RHON), rowN, tx, gx, gy);
-    const T is = rsqrt_pos(gx * gx + gy * gy + c.eps2);
     const int rn = ring_row<RING>(rowN);
-    T mx = gx * is, my = gy * is;
-    if (MASK) {
-      // a solid site (rho^N = 0/0) marks m as well: its stencil sums mix
-      // fluid taps and are finite when the site has fluid all round
-      const T r0 = sm.at(F_RHON, rn, tx);
-      if (!(r0 == r0)) mx = my = __builtin_nan("");
-    }
+    T mx, my;
+    director<MASK>(c, gx, gy, MASK ? sm.at(F_RHON, rn, tx) : T(0), mx, my);
     sm.at(F_MX, rn, tx) = mx;
     sm.at(F_MY, rn, tx) = my;
     sm.at(F_GNX, rn, tx) = gx;
@@ -886,9 +939,7 @@ __device__ __forceinline__ void march_iter(int it, const StepArgs<T>& a, const v
     const int ru = ring_row<RING>(rowU);
     const T rR = sm.at(F_RR, ru, tx), rB = sm.at(F_RB, ru, tx);
     const T rho = rR + rB;
-    T phi = c.c06R * rR + c.phiB * rB - rho * T(1.0 / 3.0);
-    if (MASK && rho == T(0)) phi = __builtin_nan("");  // solid site: the stencils' marker
-    sm.at(F_PHI, ru, tx) = phi;
+    sm.at(F_PHI, ru, tx) = phi_prime<MASK>(c, rR, rB);
     if (tx >= RG + RK && tx < NTX - RG - RK) {
       const int p = tU.phys(g);
       const bool refl = tU.refl(g);
@@ -904,18 +955,9 @@ __device__ __forceinline__ void march_iter(int it, const StepArgs<T>& a, const v
         if (t.own && v >= t.ya && v < t.yb) adj::ws_row(a.out_save, g.nx, p)[SV_K * g.nx + t.xg] = K;
       }
       const T gnx = sm.at(F_GNX, ru, tx), gny = sm.at(F_GNY, ru, tx);
-      T Gx = c.half_sigma * K * gnx + c.gx;
-      T Gy = c.half_sigma * K * gny + (refl ? -c.gy : c.gy);
-      if (a.force) {
-        Gx += st.fx[S & 1];
-        Gy += refl ? -st.fy[S & 1] : st.fy[S & 1];
-      }
-      T jx, jy;
-      momenta(rf, jx, jy);
-      if (refl) jy = -jy;   // mirror image: the y-momentum changes sign
-      const T ir = recip(rho);
-      T ux = (jx + T(0.5) * Gx) * ir, uy = (jy + T(0.5) * Gy) * ir;
-      if (MASK && rho == T(0)) ux = uy = __builtin_nan("");  // solid site (1/0 need not give NaN)
+      T Gx, Gy, ir, ux, uy;
+      force_velocity<MASK>(c, K, gnx, gny, a.force != nullptr, st.fx[S & 1], st.fy[S & 1], refl, rf, rho, Gx, Gy, ir,
+                           ux, uy);
       sm.at(F_UX, ru, tx) = ux;
       sm.at(F_UY, ru, tx) = uy;
       sm.at(F_GX, ru, tx) = Gx;

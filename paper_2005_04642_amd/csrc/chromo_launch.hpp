@@ -8,6 +8,7 @@
 #include "chromo_adjoint.hpp"
 #include "chromo_host.hpp"
 #include "chromo_solid.hpp"
+#include "chromo_tile.hpp"
 
 namespace chromo {
 namespace launch {
@@ -90,8 +91,38 @@ hipError_t march(const StepArgs<typename S::math>& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The tile kernel (chromo_tile.hpp) at a.g.tile region rows per wave.
+template <typename S, int NSLOT, int MODE, bool MASK>
+hipError_t tile_shape(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
+  constexpr int NWV = TILE_WAVES;
+  const int ntiles = a.g.nstrips * a.g.nchunks;
+  const int nblocks = 8 * ((ntiles + 7) / 8);
+  const Radii rr = {r[0], r[1], r[2], r[3]};
+  if constexpr (!MASK) {
+    if (a.g.walls) {
+      hipLaunchKernelGGL((chromo_tile_kernel<S, NWV, NSLOT, true, MODE>), dim3(nblocks), dim3(64 * NWV), 0, s, a, rr);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((chromo_tile_kernel<S, NWV, NSLOT, false, MODE, MASK>), dim3(nblocks), dim3(64 * NWV), 0, s, a,
+                     rr);
+  return hipGetLastError();
+}
+
+template <typename S, int MODE, bool MASK = false>
+hipError_t tile_launch(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
+  if constexpr (!Shape<S>::f64) {
+    if (a.g.tile == 3) return tile_shape<S, 3, MODE, MASK>(a, r, s);
+  }
+  if (a.g.tile == 2) return tile_shape<S, 2, MODE, MASK>(a, r, s);
+  return hipErrorInvalidValue;
+}
+
 template <typename S, int MODE>
 hipError_t dispatch_radii(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
+  if constexpr (MODE != MODE_ADJ) {
+    if (a.g.tile) return tile_launch<S, MODE>(a, r, s);
+  }
   const int code = (r[0] == 3) * 8 + (r[1] == 3) * 4 + (r[2] == 3) * 2 + (r[3] == 3);
 #define CHROMO_CASE(C, A, B, P, U) \
   case C:                          \
@@ -182,7 +213,7 @@ hipError_t mass(const lbm_params& p, const Geom& g, const void* pops, double* pa
 // passes 2-5 of the adjoint, with the lattice kind (periodic, walled, or with
 // a mask of solid sites: M) fixed at compile time
 template <typename T, bool W, bool M>
-void adjoint_tail(const StepArgs<T>& a, const Geom& g, const adj::Radii& r, T sigma, const T* sv, const T* A, T* B,
+void adjoint_tail(const StepArgs<T>& a, const Geom& g, const Radii& r, T sigma, const T* sv, const T* A, T* B,
                   T* C, T* D, double* part, double* dsigma, T* dforce, T* lam_out, const unsigned char* solid,
                   hipStream_t s) {
   const dim3 grid((g.nx + 255) / 256, g.ny);
@@ -246,7 +277,7 @@ hipError_t adjoint(const lbm_params& p, const Geom& g0, const void* pops, const 
   a.bnc = bnc;
   hipError_t e = solid ? march_adj_masked<S>(a, p.stencil, s) : dispatch_radii<S, MODE_ADJ>(a, p.stencil, s);
   if (e != hipSuccess) return e;
-  const adj::Radii r = {p.stencil[0], p.stencil[1], p.stencil[2], p.stencil[3]};
+  const Radii r = {p.stencil[0], p.stencil[1], p.stencil[2], p.stencil[3]};
   T* dfo = static_cast<T*>(dforce);
   T* lo = static_cast<T*>(lam_out);
   if (solid) {
@@ -411,6 +442,7 @@ hipError_t solid_fused(const lbm_params& p, const Geom& g, const void* src, void
   const int ntiles = a.g.nstrips * a.g.nchunks;
   const int nblocks = 8 * ((ntiles + 7) / 8);
   const int* r = p.stencil;
+  if (a.g.tile && special_profile(r)) return tile_launch<S, MODE_STEP, true>(a, r, s);
   if (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3) {
     hipLaunchKernelGGL((chromo_step_kernel<S, NTX, NR, 3, 3, 3, 3, false, MODE_STEP, true>), dim3(nblocks),
                        dim3(NTX * NR), 0, s, a);

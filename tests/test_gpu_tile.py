@@ -1,0 +1,66 @@
+"""The tile kernel against the march: the two forms of the step share a site's
+arithmetic, so states and fields are equal bit for bit.
+
+A plan for one CU sends a lattice of a few tiles through the march, the plan
+for the whole device through the tiles."""
+import itertools
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import *  # noqa: F401,F403
+from paper_2005_04642_amd import lbm, workloads as Wk
+
+pytestmark = pytest.mark.gpu
+
+PROFILES = [tuple(p) for p in itertools.product((1, 3), repeat=4)]
+
+
+def run(nx, ny, storage, ncu, steps=3, stencil=(3, 3, 3, 3), walls=False, solid=False, force=False, **kw):
+    p = Wk.base_params(Lambda=10.0, sigma=0.01, stencil=stencil)
+    p.update(walls=walls, gx=1e-6 if walls else 0.0, gy=-2e-6 if walls else 0.0, **kw)
+    y, x = np.mgrid[0:ny, 0:nx]
+    rn = np.tanh((0.3 * min(nx, ny) - np.hypot(x - 0.4 * nx, y - 0.6 * ny)) / 2.0)
+    mask = Wk.random_solid_sites(nx, ny, nx * ny // 15, 3) if solid else None
+    f = 1e-5 * np.random.default_rng(5).standard_normal((2, ny, nx)) if force else None
+    s = lbm.Simulation(nx, ny, p, rn, storage=storage, force=f, solid=mask)
+    s.set_cu_budget(step=ncu)
+    s.step(steps)
+    rows = slice(1, -1) if walls else slice(None)
+    state = s.live_words()[:, rows].contiguous().view(torch.uint8).cpu()
+    fields = {k: v.cpu() for k, v in s.fields().items()}
+    s.close()
+    return state, fields
+
+
+def check(nx, ny, storage, **kw):
+    a, fa = run(nx, ny, storage, 0, **kw)
+    b, fb = run(nx, ny, storage, 1, **kw)
+    assert torch.equal(a, b)
+    for k in fa:
+        assert torch.equal(fa[k].nan_to_num(nan=7.0), fb[k].nan_to_num(nan=7.0)), k
+
+
+# one strip and two of 46 columns; chunks of one tile height (14 or 30 rows),
+# one row more, and a last chunk of one row; the widest lattice of two and
+# three rounds on 256 CUs
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16", "bf16"])
+@pytest.mark.parametrize("nx,ny", [(46, 75), (47, 85), (93, 61), (64, 64), (13, 200), (700, 333)])
+def test_tile_equals_march(nx, ny, storage):
+    check(nx, ny, storage)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16"])
+@pytest.mark.parametrize("kind", [dict(walls=True), dict(solid=True), dict(force=True), dict(walls=True, force=True),
+                                  dict(fixed_K=0.02), dict(ghost_eq=1, recolor=False)],
+                         ids=lambda d: "-".join(d))
+@pytest.mark.parametrize("nx,ny", [(47, 85), (301, 147)])
+def test_tile_equals_march_options(nx, ny, storage, kind):
+    check(nx, ny, storage, **kind)
+
+
+@pytest.mark.parametrize("stencil", PROFILES, ids=lambda p: "".join(map(str, p)))
+def test_tile_equals_march_profiles(stencil):
+    check(131, 97, "f32", stencil=stencil)
+    check(131, 97, "f64", stencil=stencil, walls=True)
