@@ -147,15 +147,15 @@ chromo::Geom plan_march(const lbm_params& p, int ncu, int ntx) {
   return g;
 }
 
-// Tiles of 64 - 2H columns and at most TILE_WAVES * slots - 2H rows, one
-// workgroup per CU at a time: as many equal chunks as fill the rounds of
-// workgroups that the tallest tiles need, none below 4 rows (64^2 FP32: 6.8 us
-// per step at 4 rows, 8.3 at 14, 6.7 at 2).
-chromo::Geom plan_tile(const lbm_params& p, int ncu, int slots, int* rounds) {
+// Tiles of 64 - 2H columns and at most waves * slots - 2H rows, one workgroup
+// per CU at a time: as many equal chunks as fill the rounds of workgroups that
+// the tallest tiles need, none below 4 rows (64^2 FP32: 6.8 us per step at 4
+// rows, 8.3 at 14, 6.7 at 2).
+chromo::Geom plan_tile(const lbm_params& p, int ncu, int waves, int slots, int* rounds) {
   chromo::Geom g = geom_of(p);
   g.tile = slots;
   cut_columns(g, 64 - 2 * halo(p));
-  const int tymax = chromo::TILE_WAVES * slots - 2 * halo(p);
+  const int tymax = waves * slots - 2 * halo(p);
   const int minch = (g.F + tymax - 1) / tymax;
   *rounds = (int)(((long long)g.nstrips * minch + ncu - 1) / ncu);
   const int fill = (int)((long long)*rounds * ncu / g.nstrips);
@@ -163,32 +163,32 @@ chromo::Geom plan_tile(const lbm_params& p, int ncu, int slots, int* rounds) {
   return g;
 }
 
-// Launch plan of the step and the fields: tiles (chromo_tile.hpp) for lattices
-// of a few rounds of workgroups, the march (chromo_kernels.hpp) above.  A tile
-// has no pipeline to fill but gathers more halo rows, which costs more than
-// the fill once the march's chunks are tall.  Measured per step on 256 CUs,
-// march against tile, periodic lattices: FP32 64^2 16.0 / 6.8 us, 256^2
-// 18.0 / 8.5, 512^2 22.1 / 14.5, 724^2 (2 rounds) 30.4 / 26.7, 900^2 (3)
-// 37.6 / 40.3; FP16 724^2 (2) 27.4 / 21.9, 900^2 (3) 34.4 / 32.4, 1024^2 (4)
-// 38.0 / 41.2; FP64 64^2 15.9 / 10.5, 512^2 (2) 39.3 / 29.4, 724^2 (4)
-// 58.7 / 57.3, 900^2 (6) 84.0 / 85.9.  Two region rows per wave where one
-// round of the shorter tiles holds the lattice (64^2 FP32: 6.8 us against 8.0
-// with three), else three (512^2: 14.5 against 16.8); FP64 has registers for two.
-chromo::Geom plan(const lbm_params& p, int ncu) {
+// Launch plan of the step and the fields, or (adjoint) of the adjoint's pass
+// 1: tiles (chromo_tile.hpp) for lattices of a few rounds of workgroups, the
+// march (chromo_kernels.hpp) above.  A tile has no pipeline to fill but
+// gathers more halo rows, which costs more than the fill once the march's
+// chunks are tall.  Measured per step on 256 CUs, march against tile, periodic
+// lattices: FP32 64^2 16.0 / 6.8 us, 256^2 18.0 / 8.5, 512^2 22.1 / 14.5,
+// 724^2 (2 rounds) 30.4 / 26.7, 900^2 (3) 37.6 / 40.3; FP16 724^2 (2) 27.4 /
+// 21.9, 900^2 (3) 34.4 / 32.4, 1024^2 (4) 38.0 / 41.2; FP64 64^2 15.9 / 10.5,
+// 512^2 (2) 39.3 / 29.4, 724^2 (4) 58.7 / 57.3, 900^2 (6) 84.0 / 85.9.  Two
+// region rows per wave where one round of the shorter tiles holds the lattice
+// (64^2 FP32: 6.8 us against 8.0 with three), else three (512^2: 14.5 against
+// 16.8); FP64 has registers for two, pass 1 in FP64 for four in each of 8
+// waves.
+chromo::Geom plan(const lbm_params& p, int ncu, bool adjoint = false) {
+  const bool f64 = p.storage == LBM_STORAGE_F64;
+  const int waves = chromo::tile_waves(f64, adjoint);
   int rounds = 0;
-  chromo::Geom g = plan_tile(p, ncu, 2, &rounds);
-  if (p.storage == LBM_STORAGE_F64) {
+  chromo::Geom g = plan_tile(p, ncu, waves, f64 && adjoint ? 4 : 2, &rounds);
+  if (f64) {
     if (rounds <= 4) return g;
   } else {
     if (rounds == 1) return g;
-    g = plan_tile(p, ncu, 3, &rounds);
+    g = plan_tile(p, ncu, waves, 3, &rounds);
     if (rounds <= (p.storage == LBM_STORAGE_F32 ? 2 : 3)) return g;
   }
-  return plan_march(p, ncu, chromo::ntx_for(p.storage));
-}
-
-chromo::Geom plan_adjoint(const lbm_params& p, int ncu) {
-  return plan_march(p, ncu, chromo::ntx_for(p.storage, true));
+  return plan_march(p, ncu, chromo::ntx_for(p.storage, adjoint));
 }
 
 // ---------------------------------------------------------------------------
@@ -328,7 +328,7 @@ int lbm_init(const lbm_params* p, const void* rhoN0, const void* force, void* po
   h->force = force;
   h->steps = 0;
   h->g = plan(*p, ncu > 0 ? ncu : 1);
-  h->g_adj = plan_adjoint(*p, ncu > 0 ? ncu : 1);
+  h->g_adj = plan(*p, ncu > 0 ? ncu : 1, true);
   h->ops = ops_of(p->storage);
   h->scratch = scr;
 
@@ -352,7 +352,7 @@ int lbm_set_cu_budget(lbm_handle* h, int32_t ncu_step, int32_t ncu_adjoint) {
   const int bs = ncu_step > 0 ? std::min(ncu_step, ncu) : ncu;
   const int ba = ncu_adjoint > 0 ? std::min(ncu_adjoint, ncu) : ncu;
   h->g = plan(h->p, bs);
-  h->g_adj = plan_adjoint(h->p, ba);
+  h->g_adj = plan(h->p, ba, true);
   return LBM_OK;
 }
 
@@ -865,7 +865,7 @@ int lbm_batch_init(const lbm_params* p, int nsim, const void* const* rhoN0, void
     h.force = nullptr;
     h.steps = 0;
     h.g = plan(p[k], ncu);
-    h.g_adj = plan_adjoint(p[k], ncu);
+    h.g_adj = plan(p[k], ncu, true);
     h.ops = b->ops;
     hipError_t e = b->ops->init(p[k], h.g, rhoN0[k], h.pops[0], stream);
     if (e != hipSuccess) {

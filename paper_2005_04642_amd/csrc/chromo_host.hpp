@@ -24,8 +24,10 @@ constexpr int NR_F64 = 4;
 // and backward values of a site at once: 512 threads leave 256 VGPRs.
 constexpr int NTX_ADJ_F32 = 128;
 
-// Waves of a tile kernel workgroup (Geom::tile gives the region rows per wave).
-constexpr int TILE_WAVES = 16;
+// Waves of a tile kernel workgroup (Geom::tile gives the region rows per
+// wave).  16 waves leave 128 VGPRs each: the adjoint's pass 1 in double needs
+// more and takes 8 waves.
+constexpr int tile_waves(bool f64, bool adjoint) { return f64 && adjoint ? 8 : 16; }
 
 // Stencil profiles with instantiations of the step kernel's mask variant, the
 // walled batch kernel and the masked adjoint: (3,3,3,3), the "fast" (3,1,3,1)

@@ -94,7 +94,7 @@ hipError_t march(const StepArgs<typename S::math>& a, hipStream_t s) {
 // The tile kernel (chromo_tile.hpp) at a.g.tile region rows per wave.
 template <typename S, int NSLOT, int MODE, bool MASK>
 hipError_t tile_shape(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
-  constexpr int NWV = TILE_WAVES;
+  constexpr int NWV = tile_waves(Shape<S>::f64, MODE == MODE_ADJ);
   const int ntiles = a.g.nstrips * a.g.nchunks;
   const int nblocks = 8 * ((ntiles + 7) / 8);
   const Radii rr = {r[0], r[1], r[2], r[3]};
@@ -111,6 +111,10 @@ hipError_t tile_shape(const StepArgs<typename S::math>& a, const int* r, hipStre
 
 template <typename S, int MODE, bool MASK = false>
 hipError_t tile_launch(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
+  if constexpr (Shape<S>::f64 && MODE == MODE_ADJ) {
+    if (a.g.tile == 4) return tile_shape<S, 4, MODE, MASK>(a, r, s);
+    return hipErrorInvalidValue;
+  }
   if constexpr (!Shape<S>::f64) {
     if (a.g.tile == 3) return tile_shape<S, 3, MODE, MASK>(a, r, s);
   }
@@ -120,9 +124,7 @@ hipError_t tile_launch(const StepArgs<typename S::math>& a, const int* r, hipStr
 
 template <typename S, int MODE>
 hipError_t dispatch_radii(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
-  if constexpr (MODE != MODE_ADJ) {
-    if (a.g.tile) return tile_launch<S, MODE>(a, r, s);
-  }
+  if (a.g.tile) return tile_launch<S, MODE>(a, r, s);
   const int code = (r[0] == 3) * 8 + (r[1] == 3) * 4 + (r[2] == 3) * 2 + (r[3] == 3);
 #define CHROMO_CASE(C, A, B, P, U) \
   case C:                          \
@@ -235,6 +237,7 @@ hipError_t march_adj_masked(const StepArgs<typename S::math>& a, const int* r, h
   constexpr int NTX = Shape<S, MODE_ADJ>::ntx, NR = Shape<S, MODE_ADJ>::nr;
   const int ntiles = a.g.nstrips * a.g.nchunks;
   const int nblocks = 8 * ((ntiles + 7) / 8);
+  if (a.g.tile && special_profile(r)) return tile_launch<S, MODE_ADJ, true>(a, r, s);
   if (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3) {
     hipLaunchKernelGGL((chromo_step_kernel<S, NTX, NR, 3, 3, 3, 3, false, MODE_ADJ, true>), dim3(nblocks),
                        dim3(NTX * NR), 0, s, a);

@@ -8,7 +8,7 @@
 // a site hands from one phase to the next stays in its thread's registers;
 // only the six stencil operands go through LDS.  Four phases, three barriers:
 //   gather of the whole region, colour densities, rho^N, Phi' (all rows' words
-//     in flight at once);
+//     in flight at once in the step);
 //   grad rho^N and the director, on the region less r_g;
 //   curvature, force and velocity, on the tile and r_u more;
 //   correction, collision, recolour and store of the tile.
@@ -111,7 +111,6 @@ __global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typen
   }
   // ---- gather: colour densities, rho^N, Phi' --------------------------------
   {
-    typename ST::W pw[NSLOT][ST::NW];
     unsigned bits[NSLOT];
     if constexpr (MASK) {
 #pragma unroll
@@ -125,18 +124,25 @@ __global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typen
         fy[k] = a.force[g.plane + site];
       }
     }
+    // rows whose words are in flight together: all of them, fewer where the
+    // local backward needs the registers
+    constexpr int GD = MODE == MODE_ADJ ? (NSLOT % 2 ? 1 : 2) : NSLOT;
 #pragma unroll
-    for (int k = 0; k < NSLOT; ++k)
-      gather_words<ST, WALLS, MASK>(src, g, prow[k], t.cols, pw[k], MASK ? bits[k] : 0u);
+    for (int k0 = 0; k0 < NSLOT; k0 += GD) {
+      typename ST::W pw[GD][ST::NW];
 #pragma unroll
-    for (int k = 0; k < NSLOT; ++k) {
-      const int q = t.ty + NWV * k;
-      T pr[9], pb[9];
-      decode<ST>(pw[k], c, pr, pb, f[k]);
-      rR[k] = density(pr);
-      rB[k] = density(pb);
-      sm.d[T_RHON][q][tx] = colour_index(rR[k] * c.inv_rho0R, rB[k] * c.inv_rho0B);
-      if (MODE != MODE_FIELDS) sm.d[T_PHI][q][tx] = phi_prime<MASK>(c, rR[k], rB[k]);
+      for (int j = 0; j < GD; ++j)
+        gather_words<ST, WALLS, MASK>(src, g, prow[k0 + j], t.cols, pw[j], MASK ? bits[k0 + j] : 0u);
+#pragma unroll
+      for (int j = 0; j < GD; ++j) {
+        const int k = k0 + j, q = t.ty + NWV * k;
+        T pr[9], pb[9];
+        decode<ST>(pw[j], c, pr, pb, f[k]);
+        rR[k] = density(pr);
+        rB[k] = density(pb);
+        sm.d[T_RHON][q][tx] = colour_index(rR[k] * c.inv_rho0R, rB[k] * c.inv_rho0B);
+        if (MODE != MODE_FIELDS) sm.d[T_PHI][q][tx] = phi_prime<MASK>(c, rR[k], rB[k]);
+      }
     }
   }
   __syncthreads();

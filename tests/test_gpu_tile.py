@@ -64,3 +64,53 @@ def test_tile_equals_march_options(nx, ny, storage, kind):
 def test_tile_equals_march_profiles(stencil):
     check(131, 97, "f32", stencil=stencil)
     check(131, 97, "f64", stencil=stencil, walls=True)
+
+
+def adjoint(nx, ny, storage, ncu, stencil=(3, 3, 3, 3), walls=False, solid=False, force=False, **kw):
+    p = Wk.base_params(Lambda=10.0, sigma=0.01, stencil=stencil)
+    p.update(walls=walls, gx=1e-6 if walls else 0.0, **kw)
+    rng = np.random.default_rng(11)
+    y, x = np.mgrid[0:ny, 0:nx]
+    rn = np.tanh((0.3 * min(nx, ny) - np.hypot(x - 0.4 * nx, y - 0.6 * ny)) / 2.0)
+    mask = Wk.random_solid_sites(nx, ny, nx * ny // 15, 3) if solid else None
+    f = 1e-5 * rng.standard_normal((2, ny, nx)) if force else None
+    s = lbm.Simulation(nx, ny, p, rn, storage=storage, force=f, solid=mask)
+    s.step(4)
+    lam = s.pops_like()
+    lam.copy_(torch.as_tensor(1e-3 * rng.standard_normal((2, 9, ny, nx))))
+    out, state = s.pops_like(), s.pops_like()
+    state.copy_(s.live_pops())
+    dsigma = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    dforce = torch.zeros((2, ny, nx), dtype=s.dtype, device="cuda:0")
+    s.set_cu_budget(adjoint=ncu)
+    for _ in range(2):
+        s.adjoint_step(state, lam, out, dsigma, dforce)
+    res = [t.cpu() for t in (out, dforce, dsigma)]
+    s.close()
+    return res
+
+
+def check_adjoint(nx, ny, storage, **kw):
+    a, b = (adjoint(nx, ny, storage, ncu, **kw) for ncu in (0, 1))
+    assert torch.equal(a[0], b[0])
+    assert torch.equal(a[1], b[1])
+    # FP64 sums of the sites' FP64 terms in another order: nx ny roundings
+    assert torch.allclose(a[2], b[2], rtol=nx * ny * 2.0 ** -53, atol=0.0)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("nx,ny", [(46, 75), (47, 85), (93, 61), (64, 64), (13, 200), (500, 333)])
+def test_adjoint_tile_equals_march(nx, ny, storage):
+    check_adjoint(nx, ny, storage)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("kind", [dict(walls=True), dict(solid=True), dict(force=True), dict(fixed_K=0.02),
+                                  dict(ghost_eq=1, recolor=False)], ids=lambda d: "-".join(d))
+def test_adjoint_tile_equals_march_options(storage, kind):
+    check_adjoint(131, 97, storage, **kind)
+
+
+@pytest.mark.parametrize("stencil", PROFILES, ids=lambda p: "".join(map(str, p)))
+def test_adjoint_tile_equals_march_profiles(stencil):
+    check_adjoint(131, 97, "f32", stencil=stencil)
