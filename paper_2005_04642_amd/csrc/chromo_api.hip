@@ -16,6 +16,7 @@
 
 #include "chromo_lbm.h"
 #include "chromo_adjoint.hpp"
+#include "chromo_adjtile.hpp"
 #include "chromo_host.hpp"
 #include "chromo_solid.hpp"
 
@@ -147,15 +148,14 @@ chromo::Geom plan_march(const lbm_params& p, int ncu, int ntx) {
   return g;
 }
 
-// Tiles of 64 - 2H columns and at most waves * slots - 2H rows, one workgroup
-// per CU at a time: as many equal chunks as fill the rounds of workgroups that
-// the tallest tiles need, none below 4 rows (64^2 FP32: 6.8 us per step at 4
-// rows, 8.3 at 14, 6.7 at 2).
-chromo::Geom plan_tile(const lbm_params& p, int ncu, int waves, int slots, int* rounds) {
+// Tiles of at most 64 - 2 h columns and `rows` - 2 h rows (regions of 64
+// columns and `rows` rows), one workgroup per CU at a time: as many equal
+// chunks as fill the rounds of workgroups that the tallest tiles need, none
+// below 4 rows (64^2 FP32: 6.8 us per step at 4 rows, 8.3 at 14, 6.7 at 2).
+chromo::Geom plan_tile(const lbm_params& p, int ncu, int rows, int h, int* rounds) {
   chromo::Geom g = geom_of(p);
-  g.tile = slots;
-  cut_columns(g, 64 - 2 * halo(p));
-  const int tymax = waves * slots - 2 * halo(p);
+  cut_columns(g, 64 - 2 * h);
+  const int tymax = rows - 2 * h;
   const int minch = (g.F + tymax - 1) / tymax;
   *rounds = (int)(((long long)g.nstrips * minch + ncu - 1) / ncu);
   const int fill = (int)((long long)*rounds * ncu / g.nstrips);
@@ -180,15 +180,66 @@ chromo::Geom plan(const lbm_params& p, int ncu, bool adjoint = false) {
   const bool f64 = p.storage == LBM_STORAGE_F64;
   const int waves = chromo::tile_waves(f64, adjoint);
   int rounds = 0;
-  chromo::Geom g = plan_tile(p, ncu, waves, f64 && adjoint ? 4 : 2, &rounds);
+  auto tiles = [&](int slots) {
+    chromo::Geom g = plan_tile(p, ncu, waves * slots, halo(p), &rounds);
+    g.tile = slots;
+    return g;
+  };
+  chromo::Geom g = tiles(f64 && adjoint ? 4 : 2);
   if (f64) {
     if (rounds <= 4) return g;
   } else {
     if (rounds == 1) return g;
-    g = plan_tile(p, ncu, waves, 3, &rounds);
+    g = tiles(3);
     if (rounds <= (p.storage == LBM_STORAGE_F32 ? 2 : 3)) return g;
   }
   return plan_march(p, ncu, chromo::ntx_for(p.storage, adjoint));
+}
+
+// Launch plan of the adjoint's passes 2-5: one kernel over tiles
+// (chromo_adjtile.hpp; tile = region rows per wave), or the separate passes
+// (tile = 0).  Whole adjoint steps, separate passes against one kernel, on 256
+// CUs: FP32 periodic 64^2 22.5 / 17.8 us (2 rows), 512^2 43.7 / 38.7 (3; 42.3
+// with 6), 724^2 79.3 / 64.8 (6; 69.6 with 3), 1024^2 154 / 138, 4096^2 2069 /
+// 1967; walls 64^2 65.4 / 36.4, 512^2 113 / 66.5 (3), 4096^2 4734 / 3829;
+// masked 64^2 35.7 / 22.7, 512^2 60.6 / 46.8 (3), 4096^2 2691 / 2600; FP64
+// periodic 64^2 27.6 / 26.5, 512^2 83.5 / 73.7 (6), 1448^2 675 / 592; walls
+// 512^2 147 / 133 (3); masked 64^2 43.4 / 34.4 and, past one round, 512^2 103
+// against 109 to 117: there the separate passes stay (counted for 256 CUs
+// whatever the budget, as dL/dsigma's last bit may differ between the two).
+// They also run lattices of fewer than 4 fluid rows between walls, whose mirror
+// images overlap, and workspace rows beyond 31-bit offsets.
+chromo::Geom plan_tail(const lbm_params& p, int ncu, bool masked) {
+  const chromo::Geom none = geom_of(p);
+  const bool f64 = p.storage == LBM_STORAGE_F64;
+  if (none.walls && none.F < 4) return none;
+  if ((double)chromo::adj::WS_PLANES * p.nx * (f64 ? 8 : 4) >= (double)chromo::adj::NOWHERE) return none;
+  const int h = chromo::adj::tail_halo({p.stencil[0], p.stencil[1], p.stencil[2], p.stencil[3]});
+  int rounds = 0;
+  auto tiles = [&](int slots) {
+    // (8-wave workgroups run two to a CU, but chunks cut for twice the CUs gather
+    // more halo: FP64 512^2 90 us against 74)
+    chromo::Geom g = plan_tile(p, ncu, chromo::tail_waves(f64, slots) * slots, h, &rounds);
+    g.tile = slots;
+    return g;
+  };
+  chromo::Geom g = tiles(2);
+  if (f64 && masked) {
+    int whole = 0;
+    plan_tile(p, 256, chromo::tail_waves(f64, 2) * 2, h, &whole);
+    return whole > 1 ? none : g;
+  }
+  if (rounds > 1) {
+    if (masked) {
+      g = tiles(3);
+    } else if (none.walls) {
+      g = tiles(3);
+    } else {
+      if (!f64) g = tiles(3);
+      if (f64 || rounds > 1) g = tiles(6);
+    }
+  }
+  return g;
 }
 
 // ---------------------------------------------------------------------------
@@ -233,6 +284,7 @@ struct lbm_handle {
   int64_t steps;
   chromo::Geom g;      // forward step kernel
   chromo::Geom g_adj;  // adjoint pass 1 (workgroup shape ntx_for(storage, true))
+  int ncu_adj;         // CUs its passes 2-5 are planned for (plan_tail)
   const chromo::Ops* ops;
   double* scratch = nullptr;             // this device's static scratch (lbm_step_static)
   const unsigned char* solid = nullptr;  // device mask of solid sites (lbm_set_solid), or null
@@ -329,6 +381,7 @@ int lbm_init(const lbm_params* p, const void* rhoN0, const void* force, void* po
   h->steps = 0;
   h->g = plan(*p, ncu > 0 ? ncu : 1);
   h->g_adj = plan(*p, ncu > 0 ? ncu : 1, true);
+  h->ncu_adj = ncu > 0 ? ncu : 1;
   h->ops = ops_of(p->storage);
   h->scratch = scr;
 
@@ -353,6 +406,7 @@ int lbm_set_cu_budget(lbm_handle* h, int32_t ncu_step, int32_t ncu_adjoint) {
   const int ba = ncu_adjoint > 0 ? std::min(ncu_adjoint, ncu) : ncu;
   h->g = plan(h->p, bs);
   h->g_adj = plan(h->p, ba, true);
+  h->ncu_adj = ba;
   return LBM_OK;
 }
 
@@ -488,7 +542,8 @@ int lbm_adjoint_step(lbm_handle* h, const void* pops_t, const void* adj_next, vo
   int st = adjoint_args(h, adj_next, adj_out, workspace, ws_bytes);
   if (st != LBM_OK) return st;
   if (!pops_t) return fail(LBM_EINVAL, "pops_t must be non-NULL");
-  hipError_t e = h->ops->adjoint(h->p, h->g_adj, pops_t, h->force, adj_next, adj_out, workspace, dL_dsigma_dev,
+  const chromo::Geom gt = plan_tail(h->p, h->ncu_adj, h->solid != nullptr);
+  hipError_t e = h->ops->adjoint(h->p, h->g_adj, gt, false, true, pops_t, h->force, adj_next, adj_out, workspace, dL_dsigma_dev,
                                  dL_dforce_dev, h->solid, bounce_bits(h), stream);
   if (e != hipSuccess) return fail(LBM_EHIP, "adjoint launch: %s", hipGetErrorString(e));
   return LBM_OK;
@@ -504,10 +559,11 @@ int lbm_adjoint_steps(lbm_handle* h, int32_t nsteps, const void* const* states, 
   if (nsteps > 0 && !states) return fail(LBM_EINVAL, "states must be non-NULL");
   for (int j = 0; j < nsteps; ++j)
     if (!states[j]) return fail(LBM_EINVAL, "states[%d] is NULL", j);
+  const chromo::Geom gt = plan_tail(h->p, h->ncu_adj, h->solid != nullptr);
   for (int k = 0; k < nsteps; ++k) {
     const void* in = (k & 1) ? adj_b : adj_a;
     void* out = (k & 1) ? adj_a : adj_b;
-    hipError_t e = h->ops->adjoint(h->p, h->g_adj, states[nsteps - 1 - k], h->force, in, out, workspace,
+    hipError_t e = h->ops->adjoint(h->p, h->g_adj, gt, k > 0, k == nsteps - 1, states[nsteps - 1 - k], h->force, in, out, workspace,
                                    dL_dsigma_dev, dL_dforce_dev, h->solid, bounce_bits(h), stream);
     if (e != hipSuccess) return fail(LBM_EHIP, "adjoint launch: %s", hipGetErrorString(e));
   }
@@ -866,6 +922,7 @@ int lbm_batch_init(const lbm_params* p, int nsim, const void* const* rhoN0, void
     h.steps = 0;
     h.g = plan(p[k], ncu);
     h.g_adj = plan(p[k], ncu, true);
+    h.ncu_adj = ncu;
     h.ops = b->ops;
     hipError_t e = b->ops->init(p[k], h.g, rhoN0[k], h.pops[0], stream);
     if (e != hipSuccess) {

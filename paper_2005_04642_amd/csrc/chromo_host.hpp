@@ -29,6 +29,9 @@ constexpr int NTX_ADJ_F32 = 128;
 // more and takes 8 waves.
 constexpr int tile_waves(bool f64, bool adjoint) { return f64 && adjoint ? 8 : 16; }
 
+// The same of the kernel that runs the adjoint's passes 2-5 (chromo_adjtile.hpp).
+constexpr int tail_waves(bool f64, int slots) { return slots == 6 ? 8 : (slots == 3 && f64 ? 12 : 16); }
+
 // Stencil profiles with instantiations of the step kernel's mask variant, the
 // walled batch kernel and the masked adjoint: (3,3,3,3), the "fast" (3,1,3,1)
 // and the "compact" (1,1,1,1).
@@ -54,8 +57,11 @@ struct Ops {
                      hipStream_t s);
   // adjoint (F64/F32, periodic or walled; null for formats without it)
   // g: geometry planned for the adjoint workgroup shape (ntx_for(storage, true))
-  hipError_t (*adjoint)(const lbm_params& p, const Geom& g, const void* pops, const void* force,
-                        const void* lam_next, void* lam_out, void* ws, double* dsigma, void* dforce,
+  // gt: tiles of the fused passes 2-5 (gt.tile = 0: the separate passes).  The
+  // fused passes leave dL/dsigma in parts: add_own adds them up in this call,
+  // else the next call on the same workspace must, with add_previous
+  hipError_t (*adjoint)(const lbm_params& p, const Geom& g, const Geom& gt, bool add_previous, bool add_own,
+                        const void* pops, const void* force, const void* lam_next, void* lam_out, void* ws, double* dsigma, void* dforce,
                         const unsigned char* solid, const unsigned char* bnc, hipStream_t s);
   hipError_t (*rhoN_adjoint)(const lbm_params& p, const Geom& g, const void* pops, const void* lrN, void* out,
                              const unsigned char* solid, const unsigned char* bnc, hipStream_t s);

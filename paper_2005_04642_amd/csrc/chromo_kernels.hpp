@@ -78,6 +78,16 @@ struct Geom {
   int nr_mod;              // rows per march iteration, modulo period
 };
 
+namespace adj {
+// Parts of dL/dsigma that the tiles of one step left in its workspace.
+template <typename T>
+struct SigmaParts {
+  T* ws;
+  Geom g;          // the tiles (nstrips, nchunks) and nx
+  double* dsigma;  // the caller's accumulator
+};
+}  // namespace adj
+
 template <typename T>
 struct StepArgs {
   const void* src;              // population buffers (storage format)
@@ -95,6 +105,7 @@ struct StepArgs {
   const T* lam_next;
   T* out_save;
   T* out_adj;
+  adj::SigmaParts<T> prev;      // parts of dL/dsigma the step before left, added up beside pass 1 (ws null: none)
   // solid sites anywhere: per site, bit i - 1 set when the source r - c_i of
   // link i is solid (all set at a solid site); [ny][nx] bytes, or null
   const unsigned char* bnc;
@@ -1053,6 +1064,71 @@ __device__ __forceinline__ void march_tile(const StepArgs<typename ST::math>& a,
   }
 }
 
+// An FP64 sum carried in two doubles (the rounded sum and what its rounding
+// left out): rounded to one double at the end, a sum of FP64 terms is the same
+// for every order of the terms, hence for every cut of a lattice into tiles.
+struct Sum2 {
+  double hi, lo;
+};
+__device__ __forceinline__ Sum2 two_sum(double a, double b) {
+  const double s = a + b;
+  const double t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+__device__ __forceinline__ Sum2 add2(const Sum2& a, const Sum2& b) {
+  Sum2 s = two_sum(a.hi, b.hi);
+  const Sum2 t = two_sum(a.lo, b.lo);
+  s = two_sum(s.hi, s.lo + t.hi);
+  return two_sum(s.hi, s.lo + t.lo);
+}
+__device__ __forceinline__ Sum2 wave_sum2(Sum2 v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = add2(v, {__shfl_xor(v.hi, off, 64), __shfl_xor(v.lo, off, 64)});
+  return v;
+}
+
+namespace adj {
+
+// Where the tile (strip, chunk) of passes 2-5 leaves its part of dL/dsigma: at
+// the start of the planes that the separate passes 2-4 would use (from plane
+// PART_PLANE on) of workspace row `chunk`.
+constexpr int PART_PLANE = SV_N + A_N;
+template <typename T>
+__device__ __forceinline__ Sum2* sigma_part(T* ws, const Geom& g, int strip, int chunk) {
+  const size_t at = ((size_t)chunk * WS_PLANES + PART_PLANE) * (size_t)g.nx * sizeof(T);
+  return reinterpret_cast<Sum2*>(reinterpret_cast<char*>(ws) + (at + 7) / 8 * 8) + strip;
+}
+
+template <int NT, typename T>
+__device__ __forceinline__ void add_sigma_parts(const SigmaParts<T>& p) {
+  __shared__ Sum2 red[NT / 64];
+  Sum2 v = {0.0, 0.0};
+  for (int j = threadIdx.x; j < p.g.nstrips * p.g.nchunks; j += NT)
+    v = add2(v, *sigma_part(p.ws, p.g, j % p.g.nstrips, j / p.g.nstrips));
+  v = wave_sum2(v);
+  const int lane = threadIdx.x % 64;
+  if (lane == 0) red[threadIdx.x / 64] = v;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  v = wave_sum2(lane < NT / 64 ? red[lane] : Sum2{0.0, 0.0});
+  if (lane == 0) *p.dsigma += v.hi;
+}
+
+// A pass 1 launched with parts to add has one workgroup more, the first, for
+// that: true there.  `block` becomes the workgroup's number among the others.
+template <int NT, typename T>
+__device__ __forceinline__ bool add_previous(const SigmaParts<T>& p, int& block) {
+  if (!p.ws) return false;
+  if (block == 0) {
+    add_sigma_parts<NT>(p);
+    return true;
+  }
+  block -= 1;
+  return false;
+}
+
+}  // namespace adj
+
 template <typename ST, int NTX, int NR, int RG, int RK, int RP, int RU, bool WALLS, int MODE, bool MASK = false>
 __global__ void __launch_bounds__(NTX * NR, 1) chromo_step_kernel(StepArgs<typename ST::math> a) {
   using T = typename ST::math;
@@ -1066,7 +1142,11 @@ __global__ void __launch_bounds__(NTX * NR, 1) chromo_step_kernel(StepArgs<typen
   // whose shared halo columns and boundary cache lines then meet in one L2.
   const int ntiles = g.nstrips * g.nchunks;
   const int per_xcd = (ntiles + 7) / 8;
-  const int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  int block = blockIdx.x;
+  if constexpr (MODE == MODE_ADJ) {
+    if (adj::add_previous<NTX * NR>(a.prev, block)) return;
+  }
+  const int tile = (block % 8) * per_xcd + block / 8;
   if (tile >= ntiles) return;
   march_tile<ST, NTX, NR, RG, RK, RP, RU, WALLS, MODE, MASK>(a, tile, sm);
 }
@@ -1109,6 +1189,7 @@ __global__ void __launch_bounds__(NTX * NR, 1) chromo_batch_kernel(BatchArgs<typ
     a.force = b.sims[sim].force;
     a.out_rho = a.out_ux = a.out_uy = a.out_rhoN = a.out_save = a.out_adj = nullptr;
     a.lam_next = nullptr;
+    a.prev.ws = nullptr;
     a.bnc = b.sims[sim].bnc;
     a.g = b.sims[sim].g;
     a.c = b.sims[sim].c;

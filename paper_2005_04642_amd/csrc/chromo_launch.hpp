@@ -6,6 +6,7 @@
 #include <cstring>
 
 #include "chromo_adjoint.hpp"
+#include "chromo_adjtile.hpp"
 #include "chromo_host.hpp"
 #include "chromo_solid.hpp"
 #include "chromo_tile.hpp"
@@ -76,11 +77,17 @@ Geom geom_for(const Geom& g0) {
   return g;
 }
 
+// Workgroups of a step or pass 1 kernel: whole rounds over the 8 XCDs (see the
+// kernels), and one for the previous adjoint step's dL/dsigma.
+template <typename T>
+int step_blocks(const StepArgs<T>& a) {
+  return 8 * ((a.g.nstrips * a.g.nchunks + 7) / 8) + (a.prev.ws ? 1 : 0);
+}
+
 template <typename S, int RG, int RK, int RP, int RU, int MODE>
 hipError_t march(const StepArgs<typename S::math>& a, hipStream_t s) {
   constexpr int NTX = Shape<S, MODE>::ntx, NR = Shape<S, MODE>::nr;
-  const int ntiles = a.g.nstrips * a.g.nchunks;
-  const int nblocks = 8 * ((ntiles + 7) / 8);  // whole rounds over the 8 XCDs (see the kernel)
+  const int nblocks = step_blocks(a);
   if (a.g.walls) {
     hipLaunchKernelGGL((chromo_step_kernel<S, NTX, NR, RG, RK, RP, RU, true, MODE>), dim3(nblocks),
                        dim3(NTX * NR), 0, s, a);
@@ -95,8 +102,7 @@ hipError_t march(const StepArgs<typename S::math>& a, hipStream_t s) {
 template <typename S, int NSLOT, int MODE, bool MASK>
 hipError_t tile_shape(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
   constexpr int NWV = tile_waves(Shape<S>::f64, MODE == MODE_ADJ);
-  const int ntiles = a.g.nstrips * a.g.nchunks;
-  const int nblocks = 8 * ((ntiles + 7) / 8);
+  const int nblocks = step_blocks(a);
   const Radii rr = {r[0], r[1], r[2], r[3]};
   if constexpr (!MASK) {
     if (a.g.walls) {
@@ -160,6 +166,7 @@ StepArgs<typename S::math> args(const lbm_params& p, const Geom& g, const void* 
   a.force = static_cast<const T*>(force);
   a.out_rho = a.out_ux = a.out_uy = a.out_rhoN = a.out_save = a.out_adj = nullptr;
   a.lam_next = nullptr;
+  a.prev.ws = nullptr;
   a.bnc = nullptr;
   a.g = geom_for<S>(g);
   a.c = make_coef<S>(p);
@@ -230,13 +237,45 @@ void adjoint_tail(const StepArgs<T>& a, const Geom& g, const Radii& r, T sigma, 
                      solid);
 }
 
+// passes 2-5 in one launch over tiles (adj::tail_kernel); g.tile: region rows
+// per wave.  Only the shapes that plan_tail picks for a kind of lattice exist.
+template <typename S>
+hipError_t tail_launch(const Coef<typename S::math>& c, const Geom& g, const Radii& r, typename S::math sigma,
+                       typename S::math* ws, typename S::math* dforce, typename S::math* lam_out,
+                       const unsigned char* solid, hipStream_t s) {
+  using T = typename S::math;
+  constexpr bool f64 = Shape<S>::f64;
+  const int ntiles = g.nstrips * g.nchunks;
+  const dim3 grid(8 * ((ntiles + 7) / 8));
+#define CHROMO_TAIL(SLOTS, W, M)                                                                        \
+  hipLaunchKernelGGL((adj::tail_kernel<T, tail_waves(f64, SLOTS), SLOTS, W, M>), grid,                  \
+                     dim3(64 * tail_waves(f64, SLOTS)), 0, s, g, c, sigma, r, ws, lam_out, dforce, solid); \
+  return hipGetLastError();
+  if (solid) {
+    if (g.tile == 2) { CHROMO_TAIL(2, false, true) }
+    if constexpr (!f64) {
+      if (g.tile == 3) { CHROMO_TAIL(3, false, true) }
+    }
+  } else if (g.walls) {
+    if (g.tile == 2) { CHROMO_TAIL(2, true, false) }
+    if (g.tile == 3) { CHROMO_TAIL(3, true, false) }
+  } else {
+    if (g.tile == 2) { CHROMO_TAIL(2, false, false) }
+    if constexpr (!f64) {
+      if (g.tile == 3) { CHROMO_TAIL(3, false, false) }
+    }
+    if (g.tile == 6) { CHROMO_TAIL(6, false, false) }
+  }
+#undef CHROMO_TAIL
+  return hipErrorInvalidValue;
+}
+
 // pass 1 with a mask: the step kernel's mask variant in MODE_ADJ, built for the
 // stencil profiles (3,3,3,3), (3,1,3,1) and (1,1,1,1)
 template <typename S>
 hipError_t march_adj_masked(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
   constexpr int NTX = Shape<S, MODE_ADJ>::ntx, NR = Shape<S, MODE_ADJ>::nr;
-  const int ntiles = a.g.nstrips * a.g.nchunks;
-  const int nblocks = 8 * ((ntiles + 7) / 8);
+  const int nblocks = step_blocks(a);
   if (a.g.tile && special_profile(r)) return tile_launch<S, MODE_ADJ, true>(a, r, s);
   if (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3) {
     hipLaunchKernelGGL((chromo_step_kernel<S, NTX, NR, 3, 3, 3, 3, false, MODE_ADJ, true>), dim3(nblocks),
@@ -260,9 +299,10 @@ hipError_t march_adj_masked(const StepArgs<typename S::math>& a, const int* r, h
 // doubles.
 // ---------------------------------------------------------------------------
 template <typename S>
-hipError_t adjoint(const lbm_params& p, const Geom& g0, const void* pops, const void* force, const void* lam_next,
-                   void* lam_out, void* ws, double* dsigma, void* dforce, const unsigned char* solid,
-                   const unsigned char* bnc, hipStream_t s) {
+hipError_t adjoint(const lbm_params& p, const Geom& g0, const Geom& gt0, bool add_previous, bool add_own,
+                   const void* pops, const void* force, const void* lam_next, void* lam_out,
+                   void* ws, double* dsigma, void* dforce, const unsigned char* solid, const unsigned char* bnc,
+                   hipStream_t s) {
   using T = typename S::math;
   StepArgs<T> a = args<S>(p, g0, pops, nullptr, force);
   const Geom& g = a.g;
@@ -278,11 +318,20 @@ hipError_t adjoint(const lbm_params& p, const Geom& g0, const void* pops, const 
   a.out_adj = A;
   a.lam_next = static_cast<const T*>(lam_next);
   a.bnc = bnc;
+  const Geom gt = geom_for<S>(gt0);
+  const adj::SigmaParts<T> parts = {static_cast<T*>(ws), gt, dsigma};
+  if (gt.tile && dsigma && add_previous) a.prev = parts;
   hipError_t e = solid ? march_adj_masked<S>(a, p.stencil, s) : dispatch_radii<S, MODE_ADJ>(a, p.stencil, s);
   if (e != hipSuccess) return e;
   const Radii r = {p.stencil[0], p.stencil[1], p.stencil[2], p.stencil[3]};
   T* dfo = static_cast<T*>(dforce);
   T* lo = static_cast<T*>(lam_out);
+  if (gt.tile) {
+    e = tail_launch<S>(a.c, gt, r, (T)p.sigma, static_cast<T*>(ws), dfo, lo, solid, s);
+    if (e != hipSuccess || !dsigma || !add_own) return e;
+    hipLaunchKernelGGL(adj::sigma_kernel<T>, dim3(1), dim3(adj::SIGMA_THREADS), 0, s, parts);
+    return hipGetLastError();
+  }
   if (solid) {
     adjoint_tail<T, false, true>(a, g, r, (T)p.sigma, sv, A, B, C, D, part, dsigma, dfo, lo, solid, s);
   } else if (g.walls) {
@@ -442,8 +491,7 @@ hipError_t solid_fused(const lbm_params& p, const Geom& g, const void* src, void
   constexpr int NTX = Shape<S>::ntx, NR = Shape<S>::nr;
   StepArgs<typename S::math> a = args<S>(p, g, src, dst, force);
   a.bnc = static_cast<const unsigned char*>(ws) + solid::bits_offset(g.plane, sizeof(typename S::math));
-  const int ntiles = a.g.nstrips * a.g.nchunks;
-  const int nblocks = 8 * ((ntiles + 7) / 8);
+  const int nblocks = step_blocks(a);
   const int* r = p.stencil;
   if (a.g.tile && special_profile(r)) return tile_launch<S, MODE_STEP, true>(a, r, s);
   if (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3) {

@@ -68,7 +68,11 @@ __global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typen
   // contiguous runs of tiles per XCD, as in the march
   const int ntiles = g.nstrips * g.nchunks;
   const int per_xcd = (ntiles + 7) / 8;
-  const int id = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  int block = blockIdx.x;
+  if constexpr (MODE == MODE_ADJ) {
+    if (adj::add_previous<64 * NWV>(a.prev, block)) return;
+  }
+  const int id = (block % 8) * per_xcd + block / 8;
   if (id >= ntiles) return;
 
   // fields need u at the tile's own sites only
