@@ -66,6 +66,14 @@ def test_tile_equals_march_profiles(stencil):
     check(131, 97, "f64", stencil=stencil, walls=True)
 
 
+# 3 CUs and 2 strips of columns: one chunk each, or four rounds' shorter chunks
+@pytest.mark.parametrize("storage,nx", [("f32", 300), ("f64", 90), ("f16", 300)])
+@pytest.mark.parametrize("ny", [400, 403])
+def test_march_in_rounds(storage, nx, ny):
+    a, b = (run(nx, ny, storage, ncu) for ncu in (1, 3))
+    assert torch.equal(a[0], b[0])
+
+
 def adjoint(nx, ny, storage, ncu, stencil=(3, 3, 3, 3), walls=False, solid=False, force=False, **kw):
     p = Wk.base_params(Lambda=10.0, sigma=0.01, stencil=stencil)
     p.update(walls=walls, gx=1e-6 if walls else 0.0, **kw)
