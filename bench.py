@@ -257,7 +257,7 @@ def adjoint_rollout(torch, n=512, steps=2000, checkpoint=100):
     drop_to_ellipse workload; FP32 storage, FP64 dL/dsigma.  Returns forward
     and backward (recompute + adjoint) times: the backward as the rollout runs
     it (the next segment recomputed on a second stream during the current
-    segment's adjoint steps, the two streams on disjoint CUs at this size)
+    segment's adjoint steps)
     and, for context, with both streams on every CU and on one stream."""
     from paper_2005_04642_amd import adjoint, workloads as Wk
     rn0, target, force, params = Wk.drop_to_ellipse(n)
@@ -294,7 +294,7 @@ def adjoint_rollout(torch, n=512, steps=2000, checkpoint=100):
            "MLUPS_forward": round(lups / fwd / 1e6, 1), "MLUPS_backward": round(lups / bwd / 1e6, 1),
            "ratio": round(fwd / bwd, 4), "loss": loss, "dL_dsigma": dsig}
     if checkpoint > 1:
-        res["recompute_cus"] = adjoint.RECOMPUTE_CUS if n * n <= adjoint.PARTITION_MAX_SITES else 0
+        res["recompute_cus"] = adjoint.RECOMPUTE_CUS
         # the same backward with both streams on every CU, and on one stream
         fwd2, bwd2, _, dsig2 = timed(True, 0)
         res["backward_s_two_streams_unconfined"] = round(bwd2, 3)

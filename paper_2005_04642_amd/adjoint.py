@@ -18,12 +18,13 @@ import torch
 from . import lbm
 
 
-# Backward passes of lattices up to this many sites confine the recompute to
-# the first RECOMPUTE_CUS CUs and the adjoint steps to the others (512^2 FP32
-# drop: a forward step takes 23 us on 256 CUs and 40 us on 64, the adjoint step
-# 51 us on 256 and 54 us on 192).
-PARTITION_MAX_SITES = 1 << 20
-RECOMPUTE_CUS = 64
+# CUs the backward pass confines the recompute to (the adjoint steps to the
+# others) unless told: none.  Both run as tiles on every CU (512^2 FP32: a
+# forward step 15 us, an adjoint step 39 us), and plans for a share of the CUs
+# need more rounds of tiles: 60-step 512^2 rollout with gradients 4.7 ms with
+# both streams on every CU, 5.6 ms with 64 CUs against 192, 400 steps 26.9 ms
+# against 32.1 (one stream: 4.6 and 28.1 ms).
+RECOMPUTE_CUS = 0
 
 _partitions = {}
 
@@ -102,12 +103,10 @@ class _Rollout(torch.autograd.Function):
         # buffers of their own.  With two sets, segment k - 1 is recomputed on
         # a second stream while the adjoint steps of segment k run; each set is
         # reused only after the adjoint steps that read it have finished
-        # (events).  On small lattices the two streams are confined to disjoint
+        # (events).  With recompute_cus the two streams are confined to disjoint
         # CUs (lbm_partition_stream, tiles planned for each share with
-        # lbm_set_cu_budget): there a step's march keeps each CU busy for long
-        # with one workgroup, and unconfined streams queue one kernel's
-        # workgroups behind the other's.  Same kernels in the same order on
-        # each stream: the gradients depend on none of this.
+        # lbm_set_cu_budget).  Same kernels in the same order on each stream:
+        # the gradients depend on none of this.
         longest = max(e - s for s, e in zip(starts, ends))
         per = max(longest - 1, 1)
         state_bytes = sim.ny * sim.nx * 18 * (8 if T == torch.float64 else 4)
@@ -119,7 +118,7 @@ class _Rollout(torch.autograd.Function):
         rcus = ctx.recompute_cus
         ncu = torch_.cuda.get_device_properties(sim.device).multi_processor_count // 8 * 8
         if rcus is None:
-            rcus = RECOMPUTE_CUS if sim.nx * sim.ny <= PARTITION_MAX_SITES else 0
+            rcus = RECOMPUTE_CUS
         if nsets == 1 or not 0 < rcus < ncu:
             rcus = 0
         block = torch.empty((nsets, per, sim.ny, 2, 9, sim.nx), dtype=T, device=sim.device)
@@ -211,9 +210,8 @@ def rollout(rhoN0, sigma, force, params, nsteps, checkpoint=100, storage="f32", 
     (False); None chooses True when two segments' states take at most half of
     the free device memory.  ``recompute_cus``: with the overlap, confine the
     recompute to that many CUs (a multiple of 8; multiples of 32 run best) and
-    the adjoint steps to the rest; None chooses RECOMPUTE_CUS for lattices of
-    at most PARTITION_MAX_SITES sites, 0 leaves both streams on every CU.  The
-    gradients are the same either way."""
+    the adjoint steps to the rest; None (RECOMPUTE_CUS) and 0 leave both
+    streams on every CU.  The gradients are the same either way."""
     if not torch.is_tensor(sigma):
         sigma = torch.tensor(float(sigma), dtype=torch.float64)
     return _Rollout.apply(rhoN0, sigma, force, params, int(nsteps), int(checkpoint), storage, device, overlap,
