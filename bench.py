@@ -32,7 +32,8 @@ BYTES_PER_LU = {"f32": 144, "f64": 288, "f16": 80, "bf16": 80}
 # populations in FP32, 80 B per update) are also reported
 BYTES_16BIT_POPS = 72
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2005_04642_amd", "csrc", f)
-                  for f in ("chromo_kernels.hpp", "chromo_tile.hpp", "chromo_launch.hpp", "chromo_host.hpp", "chromo_api.hip")]
+                  for f in ("chromo_kernels.hpp", "chromo_tile.hpp", "chromo_batch.hpp", "chromo_launch.hpp",
+                            "chromo_host.hpp", "chromo_api.hip")]
 
 
 STORAGE_NAME = {"f32": "FP32", "f16": "FP16-offset (16-bit words, FP32 arithmetic)",

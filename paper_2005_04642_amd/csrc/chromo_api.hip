@@ -17,6 +17,7 @@
 #include "chromo_lbm.h"
 #include "chromo_adjoint.hpp"
 #include "chromo_adjtile.hpp"
+#include "chromo_batch.hpp"
 #include "chromo_host.hpp"
 #include "chromo_solid.hpp"
 
@@ -699,7 +700,7 @@ int batch_validate(const lbm_params* p, int nsim) {
   return LBM_OK;
 }
 
-// Tile plan of one lattice for workgroup width ntx and chunk height cap.
+// March plan of one lattice for workgroup width ntx and chunk height cap.
 chromo::Geom batch_geom(const lbm_params& p, int ntx, int tycap) {
   chromo::Geom g = geom_of(p);
   cut_columns(g, ntx - 2 * halo(p));
@@ -707,32 +708,65 @@ chromo::Geom batch_geom(const lbm_params& p, int ntx, int tycap) {
   return g;
 }
 
-size_t batch_tiles(const lbm_params* p, int nsim, int ntx, int tycap) {
-  size_t n = 0;
-  for (int k = 0; k < nsim; ++k) {
-    const chromo::Geom g = batch_geom(p[k], ntx, tycap);
-    n += (size_t)g.nstrips * g.nchunks;
-  }
-  return n;
+// The same in tiles of the batch kernel (FP32 arithmetic).
+chromo::Geom batch_geom_tiles(const lbm_params& p, int tycap) {
+  chromo::Geom g = geom_of(p);
+  g.tile = 1;
+  const int rows = std::min(tycap, chromo::BATCH_TILE_ROWS - 2 * halo(p));
+  cut_columns(g, 64 - 2 * halo(p));
+  cut_rows(g, (g.F + rows - 1) / rows);
+  return g;
 }
 
+// Cost of an item of `rows` rows in quarters of a march iteration (0.85 to 1.1
+// us at 192 columns): a march is its fill and its rows, a tile its phases, the
+// wait for the stores of the tile before it, and its rows (8 us at 8 rows, 13 at
+// 16 alone in its bin, 20 as one of three).
+constexpr int BATCH_QUARTERS = 4;
+int batch_cost(const chromo::Geom& g, int rows, int nr, int it0) {
+  return g.tile ? 8 + rows : BATCH_QUARTERS * (it0 + (rows + nr - 1) / nr);
+}
+long long batch_cost(const chromo::Geom& g, int nr, int it0) {
+  const int last = g.F - (g.nchunks - 1) * g.TY;
+  return (long long)g.nstrips * ((g.nchunks - 1) * (long long)batch_cost(g, g.TY, nr, it0) +
+                                 batch_cost(g, last, nr, it0));
+}
+
+// Chunk heights a batch plan considers, up to its cap.
+const int BATCH_HEIGHTS[] = {8, 16, 32, 48, 64, 96, 128, 192, 256, 384, 512, 1 << 30};
+// and the sites up to which lattices run as tiles
+const long long BATCH_TILE_SITES[] = {0, 64 * 64, 128 * 128, 256 * 256, 1 << 20};
+
 size_t batch_items_cap(const lbm_params* p, int nsim) {
-  size_t cap = 0;
   const chromo::Ops* ops = ops_of(p[0].storage);
-  for (int i = 0; i < 3 && ops->batch_ntx[i]; ++i)
-    for (int tc : BATCH_TYCAPS) cap = std::max(cap, batch_tiles(p, nsim, ops->batch_ntx[i], tc));
+  size_t cap = 0;
+  for (int k = 0; k < nsim; ++k) {
+    size_t most = 0;
+    auto count = [&](const chromo::Geom& g) { most = std::max(most, (size_t)g.nstrips * g.nchunks); };
+    for (int i = 0; i < 3 && ops->batch_ntx[i]; ++i)
+      count(batch_geom(p[k], ops->batch_ntx[i], BATCH_HEIGHTS[0]));
+    if (ops->math_bytes == 4) count(batch_geom_tiles(p[k], BATCH_HEIGHTS[0]));
+    cap += most;
+  }
   return cap;
 }
 
 struct BatchPlan {
   int ntx = 0, tycap = 0, nbins = 0;
+  std::vector<chromo::Geom> geom;  // of every lattice
   std::vector<unsigned char> sims;
   std::vector<int> bin_start, items;
   double max_cost = 0.0;  // largest bin, in march iterations
 };
 
-// Longest-processing-time-first assignment of the tiles of every lattice to
-// nbins bins (one workgroup each), costs counted in march iterations.
+// Work items (marches or tiles) of every lattice and their assignment to nbins
+// bins (one workgroup each), longest first to the emptiest bin.  Of the chunk
+// heights up to the cap, and of the lattice sizes up to which lattices run as
+// tiles, the plan keeps the pair whose largest bin is smallest.  A batch that
+// fills the bins many times over marches (tiles gather more halo); in a small
+// one tiles of few rows use all the CUs: FP32, 256 CUs, lattices of 64^2 to
+// 512^2, against marches in chunks of 128 rows: 2 lattices 128.5 -> 11.5 us per
+// step, 5 130.7 -> 16.8.
 BatchPlan batch_plan(const lbm_params* p, int nsim, const std::vector<size_t>& off, int nbins, int ntx, int tycap,
                      const chromo::Ops& ops, int nr, int it0, const std::vector<const void*>& force,
                      const std::vector<const unsigned char*>& bnc) {
@@ -740,41 +774,70 @@ BatchPlan batch_plan(const lbm_params* p, int nsim, const std::vector<size_t>& o
   b.ntx = ntx;
   b.tycap = tycap;
   b.nbins = nbins;
-  b.sims.resize((size_t)nsim * ops.sim_desc_bytes);
-  struct Tile {
+  struct Item {
     int sim, tile;
     int cost;
   };
-  std::vector<Tile> tiles;
-  for (int k = 0; k < nsim; ++k) {
-    const chromo::Geom g = batch_geom(p[k], ntx, tycap);
-    ops.sim_desc(p[k], g, (unsigned long long)off[k], force[k], bnc[k], &b.sims[(size_t)k * ops.sim_desc_bytes]);
-    for (int t = 0; t < g.nstrips * g.nchunks; ++t) {
-      const int chunk = t / g.nstrips;
-      const int rows = std::min(g.TY, g.F - chunk * g.TY);
-      tiles.push_back({k, t, it0 + (rows + nr - 1) / nr});
-    }
-  }
-  std::stable_sort(tiles.begin(), tiles.end(), [](const Tile& a, const Tile& c) { return a.cost > c.cost; });
   typedef std::pair<long long, int> Load;  // (cost, bin)
-  std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-  for (int i = 0; i < nbins; ++i) heap.push(Load(0, i));
-  std::vector<std::vector<int>> bins(nbins);
-  for (size_t i = 0; i < tiles.size(); ++i) {
-    Load l = heap.top();
-    heap.pop();
-    bins[l.second].push_back((int)i);
-    l.first += tiles[i].cost;
-    b.max_cost = std::max(b.max_cost, (double)l.first);
-    heap.push(l);
-  }
-  b.bin_start.assign(nbins + 1, 0);
-  for (int i = 0; i < nbins; ++i) {
-    b.bin_start[i + 1] = b.bin_start[i] + (int)bins[i].size();
-    for (int j : bins[i]) {
-      b.items.push_back(tiles[j].sim);
-      b.items.push_back(tiles[j].tile);
+  std::vector<Item> items;
+  std::vector<int> bin_of;  // of every item
+  long long best = -1;
+  // the tallest chunks first: of equal plans the one with less fill stays
+  for (int ih = (int)(sizeof(BATCH_HEIGHTS) / sizeof(BATCH_HEIGHTS[0])) - 1; ih >= 0; --ih) {
+    if (ih > 0 && BATCH_HEIGHTS[ih - 1] >= tycap) continue;  // the cap itself stands for taller ones
+    const int h = std::min(BATCH_HEIGHTS[ih], tycap);
+    for (long long tiles_to : BATCH_TILE_SITES) {
+      if (tiles_to && ops.math_bytes != 4) break;
+      std::vector<chromo::Geom> geom(nsim);
+      long long total = 0, longest = 0;
+      for (int k = 0; k < nsim; ++k) {
+        chromo::Geom& g = geom[k];
+        g = (long long)p[k].nx * p[k].ny <= tiles_to ? batch_geom_tiles(p[k], h) : batch_geom(p[k], ntx, h);
+        total += batch_cost(g, nr, it0);
+        longest = std::max(longest, (long long)batch_cost(g, g.TY, nr, it0));
+      }
+      if (best >= 0 && std::max(longest, (total + nbins - 1) / nbins) >= best) continue;
+      std::vector<Item> its;
+      for (int k = 0; k < nsim; ++k) {
+        const chromo::Geom& g = geom[k];
+        for (int t = 0; t < g.nstrips * g.nchunks; ++t)
+          its.push_back({k, t, batch_cost(g, std::min(g.TY, g.F - t / g.nstrips * g.TY), nr, it0)});
+      }
+      std::stable_sort(its.begin(), its.end(), [](const Item& a, const Item& c) { return a.cost > c.cost; });
+      std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
+      for (int i = 0; i < nbins; ++i) heap.push(Load(0, i));
+      std::vector<int> bin(its.size());
+      long long most = 0;
+      for (size_t i = 0; i < its.size(); ++i) {
+        Load l = heap.top();
+        heap.pop();
+        bin[i] = l.second;
+        l.first += its[i].cost;
+        most = std::max(most, l.first);
+        heap.push(l);
+      }
+      if (best < 0 || most < best) {
+        best = most;
+        b.geom = std::move(geom);
+        items = std::move(its);
+        bin_of = std::move(bin);
+      }
     }
+  }
+  b.max_cost = (double)best / BATCH_QUARTERS;
+  b.sims.resize((size_t)nsim * ops.sim_desc_bytes);
+  for (int k = 0; k < nsim; ++k)
+    ops.sim_desc(p[k], b.geom[k], (unsigned long long)off[k], force[k], bnc[k],
+                 &b.sims[(size_t)k * ops.sim_desc_bytes]);
+  b.bin_start.assign(nbins + 1, 0);
+  for (int i : bin_of) b.bin_start[i + 1] += 1;
+  for (int i = 0; i < nbins; ++i) b.bin_start[i + 1] += b.bin_start[i];
+  b.items.resize(2 * items.size());
+  std::vector<int> at(b.bin_start.begin(), b.bin_start.end() - 1);
+  for (size_t i = 0; i < items.size(); ++i) {
+    const int j = at[bin_of[i]]++;
+    b.items[2 * j] = items[i].sim;
+    b.items[2 * j + 1] = items[i].tile;
   }
   return b;
 }
@@ -805,10 +868,10 @@ struct lbm_batch {
 namespace {
 
 // Strip widths the batch kernels of this batch may use.  With FP32 arithmetic
-// the 192-wide strips (768 threads, at most 168 VGPRs) spill registers in the
-// walled and masked variants (hipcc: 5 VGPRs for walls at stencil 3333, 13 and
-// 57 for masks at 3131 and 3333), so walled and masked batches use 128-wide
-// strips only (no spills).  Returns the count written to out.
+// the 192-wide strips (768 threads, at most 168 VGPRs) leave the walled and
+// masked variants few registers (162 VGPRs for walls at stencil 3333; masks
+// there spill 5), so walled and masked batches use 128-wide strips only.
+// Returns the count written to out.
 int batch_widths(const lbm_batch* b, int* out) {
   int n = 0;
   for (int i = 0; i < 3 && b->ops->batch_ntx[i]; ++i) {
@@ -956,7 +1019,7 @@ int lbm_batch_init(const lbm_params* p, int nsim, const void* const* rhoN0, void
   const int nw = batch_widths(b, widths);
   int ntx0 = widths[0];
   for (int i = 1; i < nw; ++i) ntx0 = std::max(ntx0, widths[i]);
-  st = batch_upload(b, batch_plan(p, nsim, b->off, ncu, ntx0, 128, *b->ops, nr, it0, b->force, b->bnc), stream);
+  st = batch_upload(b, batch_plan(p, nsim, b->off, ncu, ntx0, BATCH_TYCAPS[4], *b->ops, nr, it0, b->force, b->bnc), stream);
   if (st != LBM_OK) {
     delete b;
     return st;
@@ -1045,7 +1108,7 @@ int lbm_batch_set_force(lbm_batch* b, int32_t k, const void* force, hipStream_t 
   if (!b || k < 0 || k >= b->nsim) return fail(LBM_EINVAL, "bad batch or lattice index");
   b->force[k] = force;
   b->view[k].force = force;
-  const chromo::Geom g = batch_geom(b->p[k], b->plan.ntx, b->plan.tycap);
+  const chromo::Geom& g = b->plan.geom[k];
   unsigned char* desc = &b->plan.sims[(size_t)k * b->ops->sim_desc_bytes];
   b->ops->sim_desc(b->p[k], g, (unsigned long long)b->off[k], force, b->bnc[k], desc);
   HIP_TRY(hipMemcpyAsync(static_cast<char*>(b->d_sims) + (size_t)k * b->ops->sim_desc_bytes, desc,
@@ -1090,7 +1153,7 @@ int lbm_batch_set_solid(lbm_batch* b, int32_t k, const uint8_t* solid_dev, void*
                           stream);
     return st;
   }
-  const chromo::Geom g = batch_geom(p, b->plan.ntx, b->plan.tycap);
+  const chromo::Geom& g = b->plan.geom[k];
   unsigned char* desc = &b->plan.sims[(size_t)k * b->ops->sim_desc_bytes];
   b->ops->sim_desc(p, g, (unsigned long long)b->off[k], b->force[k], b->bnc[k], desc);
   HIP_TRY(hipMemcpyAsync(static_cast<char*>(b->d_sims) + (size_t)k * b->ops->sim_desc_bytes, desc,

@@ -1152,62 +1152,6 @@ __global__ void __launch_bounds__(NTX * NR, 1) chromo_step_kernel(StepArgs<typen
 }
 
 // ---------------------------------------------------------------------------
-// Batched step: many independent lattices in one launch.  Each
-// workgroup owns a bin of work items (lattice, tile), planned on the host so
-// that the bins' costs are balanced, and runs them one after the other.
-// ---------------------------------------------------------------------------
-template <typename T>
-struct SimDesc {
-  Geom g;                 // per-lattice geometry and tile plan
-  Coef<T> c;              // per-lattice constants
-  unsigned long long off; // byte offset of the lattice's populations in both packed buffers
-  const T* force;         // per-site force density [2][ny][nx] of the lattice, or null
-  const unsigned char* bnc;  // bounce bits of the lattice's solid-site mask, or null
-};
-
-template <typename T>
-struct BatchArgs {
-  const char* src;              // packed population buffers
-  char* dst;
-  const SimDesc<T>* sims;
-  const int* bin_start;         // [nbins + 1] offsets into items
-  const int* items;             // pairs (lattice, tile)
-};
-
-template <typename ST, int NTX, int NR, int RG, int RK, int RP, int RU, bool WALLS = false, bool MASK = false>
-__global__ void __launch_bounds__(NTX * NR, 1) chromo_batch_kernel(BatchArgs<typename ST::math> b) {
-  using T = typename ST::math;
-  using PP = Pipe<NR>;
-  static_assert(NTX > 2 * (RG + RK + RU), "strip must be wider than its halo");
-  __shared__ Smem<T, NTX, PP::RING> sm;
-  const int k0 = b.bin_start[blockIdx.x], k1 = b.bin_start[blockIdx.x + 1];
-  for (int k = k0; k < k1; ++k) {
-    const int sim = b.items[2 * k], tile = b.items[2 * k + 1];
-    StepArgs<T> a;
-    a.src = b.src + b.sims[sim].off;
-    a.dst = b.dst + b.sims[sim].off;
-    a.force = b.sims[sim].force;
-    a.out_rho = a.out_ux = a.out_uy = a.out_rhoN = a.out_save = a.out_adj = nullptr;
-    a.lam_next = nullptr;
-    a.prev.ws = nullptr;
-    a.bnc = b.sims[sim].bnc;
-    a.g = b.sims[sim].g;
-    a.c = b.sims[sim].c;
-    // in a batch with masks, lattices without one take the plain march
-    if constexpr (MASK) {
-      if (a.bnc) {
-        march_tile<ST, NTX, NR, RG, RK, RP, RU, WALLS, MODE_STEP, true>(a, tile, sm);
-      } else {
-        march_tile<ST, NTX, NR, RG, RK, RP, RU, WALLS, MODE_STEP, false>(a, tile, sm);
-      }
-    } else {
-      march_tile<ST, NTX, NR, RG, RK, RP, RU, WALLS, MODE_STEP, false>(a, tile, sm);
-    }
-    __syncthreads();  // the next tile reuses the LDS rings
-  }
-}
-
-// ---------------------------------------------------------------------------
 // streaming only (test mode): buf'_i(r) = f_i(r)
 // ---------------------------------------------------------------------------
 template <typename S>

@@ -7,6 +7,7 @@
 
 #include "chromo_adjoint.hpp"
 #include "chromo_adjtile.hpp"
+#include "chromo_batch.hpp"
 #include "chromo_host.hpp"
 #include "chromo_solid.hpp"
 #include "chromo_tile.hpp"

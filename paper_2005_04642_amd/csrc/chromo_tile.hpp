@@ -57,24 +57,14 @@ __device__ __forceinline__ T div(int r, const T* sx, const T* sy, int row, int t
 
 }  // namespace tile
 
-template <typename ST, int NWV, int NSLOT, bool WALLS, int MODE, bool MASK = false>
-__global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typename ST::math> a, Radii r) {
+// Tile `id` of one lattice.
+template <typename ST, int NWV, int NSLOT, bool WALLS, int MODE, bool MASK>
+__device__ __forceinline__ void tile_step(const StepArgs<typename ST::math>& a, const Radii& r, int id,
+                                          tile::TileSmem<typename ST::math, NWV * NSLOT>& sm) {
   using T = typename ST::math;
   using namespace tile;
-  constexpr int ROWS = NWV * NSLOT;
-  __shared__ TileSmem<T, ROWS> sm;
   const Geom& g = a.g;
   const Coef<T>& c = a.c;
-  // contiguous runs of tiles per XCD, as in the march
-  const int ntiles = g.nstrips * g.nchunks;
-  const int per_xcd = (ntiles + 7) / 8;
-  int block = blockIdx.x;
-  if constexpr (MODE == MODE_ADJ) {
-    if (adj::add_previous<64 * NWV>(a.prev, block)) return;
-  }
-  const int id = (block % 8) * per_xcd + block / 8;
-  if (id >= ntiles) return;
-
   // fields need u at the tile's own sites only
   const int ru = MODE == MODE_FIELDS ? 0 : r.u;
   const int H = r.g + r.k + ru;
@@ -130,7 +120,7 @@ __global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typen
     }
     // rows whose words are in flight together: all of them, fewer where the
     // local backward needs the registers
-    constexpr int GD = MODE == MODE_ADJ ? (NSLOT % 2 ? 1 : 2) : NSLOT;
+    constexpr int GD = MODE == MODE_ADJ ? (NSLOT % 2 ? 1 : 2) : (NSLOT > 4 ? NSLOT / 2 : NSLOT);
 #pragma unroll
     for (int k0 = 0; k0 < NSLOT; k0 += GD) {
       typename ST::W pw[GD][ST::NW];
@@ -226,6 +216,21 @@ __global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typen
                                        sm.d[T_RHON][q][tx], sm.d[T_MX][q][tx], sm.d[T_MY][q][tx], p, t, lam);
     }
   }
+}
+
+template <typename ST, int NWV, int NSLOT, bool WALLS, int MODE, bool MASK = false>
+__global__ void __launch_bounds__(64 * NWV, 1) chromo_tile_kernel(StepArgs<typename ST::math> a, Radii r) {
+  __shared__ tile::TileSmem<typename ST::math, NWV * NSLOT> sm;
+  // contiguous runs of tiles per XCD, as in the march
+  const int ntiles = a.g.nstrips * a.g.nchunks;
+  const int per_xcd = (ntiles + 7) / 8;
+  int block = blockIdx.x;
+  if constexpr (MODE == MODE_ADJ) {
+    if (adj::add_previous<64 * NWV>(a.prev, block)) return;
+  }
+  const int id = (block % 8) * per_xcd + block / 8;
+  if (id >= ntiles) return;
+  tile_step<ST, NWV, NSLOT, WALLS, MODE, MASK>(a, r, id, sm);
 }
 
 }  // namespace chromo

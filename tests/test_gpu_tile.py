@@ -122,3 +122,28 @@ def test_adjoint_tile_equals_march_options(storage, kind):
 @pytest.mark.parametrize("stencil", PROFILES, ids=lambda p: "".join(map(str, p)))
 def test_adjoint_tile_equals_march_profiles(stencil):
     check_adjoint(131, 97, "f32", stencil=stencil)
+
+
+# few lattices run as tiles, many as marches (a lattice in 24 of them as in 3)
+@pytest.mark.parametrize("storage", ["f32", "f16", "f64"])
+@pytest.mark.parametrize("count", [3, 24])
+@pytest.mark.parametrize("walls", [False, True])
+def test_batch_forms_equal_single_lattices(storage, count, walls):
+    rng = np.random.default_rng(count)
+    lats = []
+    for k in range(count):
+        nx, ny = int(rng.choice([47, 64, 131, 300])), int(rng.choice([33, 64, 97, 300]))
+        p = Wk.base_params(Lambda=10.0, sigma=0.01)
+        p.update(walls=walls, gx=1e-6 if walls else 0.0)
+        y, x = np.mgrid[0:ny, 0:nx]
+        lats.append((nx, ny, p, np.tanh((0.3 * min(nx, ny) - np.hypot(x - 0.4 * nx, y - 0.6 * ny)) / 2.0)))
+    b = lbm.Batch(lats, storage=storage)
+    b.step(4)
+    live = b.pops[b.lib.lbm_batch_current_pops(b.h)]
+    for k, (nx, ny, p, rn) in enumerate(lats):
+        s = lbm.Simulation(nx, ny, p, rn, storage=storage)
+        s.step(4)
+        want = s.pops[lbm.lbm_current_pops(s.h)].view(torch.uint8)
+        assert torch.equal(live[b.offsets[k]:b.offsets[k] + want.numel()], want), k
+        s.close()
+    b.close()
