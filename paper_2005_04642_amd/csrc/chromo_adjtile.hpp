@@ -258,6 +258,45 @@ __global__ void __launch_bounds__(64 * NWV, 1)
     }
   };
 
+  // the push's adjoints of f_i, fetched over pass 4, or, where the lattice has
+  // walls, from here: there the stencils of passes 2 and 3 take long enough to
+  // hide them (FP32 walled adjoint step 512^2 66.3 -> 62.4 us, 2048^2 947 -> 867;
+  // earlier on periodic lattices 45.6 -> 46.9, masks spill, FP64 5 % slower)
+  constexpr bool EARLY = W && sizeof(T) == 4;
+  T lf[NSLOT][9];
+  unsigned bounce[NSLOT];  // bit i: the word of link i is bounced back at its own site
+  auto load_f = [&] {
+#pragma unroll
+    for (int k = 0; k < NSLOT; ++k) {
+      const bool mine = own(k);
+      const int y = prow[k];
+      const int yp = y + 1 >= ny ? y + 1 - ny : y + 1, ym = y < 1 ? y - 1 + ny : y - 1;
+      const WsRow<T> row0(ws, g, y), rowP(ws, g, yp), rowM(ws, g, ym);
+      const int xp = xg + 1 >= nx ? xg + 1 - nx : xg + 1, xm = xg < 1 ? xg - 1 + nx : xg - 1;
+      bounce[k] = 0u;
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        const int cx = link_cx(i), cy = link_cy(i);
+        const int o = cx == 1 ? xp : (cx == -1 ? xm : xg);
+        bool b = false;
+        if constexpr (W) b = (cy == -1 && y == 1) || (cy == 1 && y == ny - 2);
+        if constexpr (M) b = mine && (i != 0) && ((wall[min(max(w + NWV * k + cy, 0), ROWS - 1)] >> (tx + cx)) & 1ull);
+        if (b) bounce[k] |= 1u << i;
+        if constexpr (W) {
+          lf[k][i] = (b ? row0 : (cy == 1 ? rowP : (cy == -1 ? rowM : row0)))
+                         .at(G_A + A_F + (b ? link_opp(i) : i), mine ? (b ? xg : o) * E : NOWHERE, g);
+        } else {
+          lf[k][i] = (cy == 1 ? rowP : (cy == -1 ? rowM : row0)).at(G_A + A_F + i, mine && !b ? o * E : NOWHERE, g);
+          if constexpr (M) {
+            const T own_word = row0.at(G_A + A_F + link_opp(i), b ? xg * E : NOWHERE, g);
+            lf[k][i] = b ? own_word : lf[k][i];
+          }
+        }
+      }
+    }
+  };
+  if constexpr (EARLY) load_f();
+
   // ---- pass 2 ---------------------------------------------------------------------
   T bgx[NSLOT], bgy[NSLOT], brr[NSLOT], brb[NSLOT];
   Sum2 acc = {0.0, 0.0};
@@ -354,37 +393,7 @@ __global__ void __launch_bounds__(64 * NWV, 1)
     sm.d[L_CX][q][tx] = cx;
     sm.d[L_CY][q][tx] = cy;
   }
-  // the push's adjoints of f_i, on their way over the next phase
-  T lf[NSLOT][9];
-  unsigned bounce[NSLOT];  // bit i: the word of link i is bounced back at its own site
-#pragma unroll
-  for (int k = 0; k < NSLOT; ++k) {
-    const bool mine = own(k);
-    const int y = prow[k];
-    const int yp = y + 1 >= ny ? y + 1 - ny : y + 1, ym = y < 1 ? y - 1 + ny : y - 1;
-    const WsRow<T> row0(ws, g, y), rowP(ws, g, yp), rowM(ws, g, ym);
-    const int xp = xg + 1 >= nx ? xg + 1 - nx : xg + 1, xm = xg < 1 ? xg - 1 + nx : xg - 1;
-    bounce[k] = 0u;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const int cx = link_cx(i), cy = link_cy(i);
-      const int o = cx == 1 ? xp : (cx == -1 ? xm : xg);
-      bool b = false;
-      if constexpr (W) b = (cy == -1 && y == 1) || (cy == 1 && y == ny - 2);
-      if constexpr (M) b = mine && (i != 0) && ((wall[min(max(w + NWV * k + cy, 0), ROWS - 1)] >> (tx + cx)) & 1ull);
-      if (b) bounce[k] |= 1u << i;
-      if constexpr (W) {
-        lf[k][i] = (b ? row0 : (cy == 1 ? rowP : (cy == -1 ? rowM : row0)))
-                       .at(G_A + A_F + (b ? link_opp(i) : i), mine ? (b ? xg : o) * E : NOWHERE, g);
-      } else {
-        lf[k][i] = (cy == 1 ? rowP : (cy == -1 ? rowM : row0)).at(G_A + A_F + i, mine && !b ? o * E : NOWHERE, g);
-        if constexpr (M) {
-          const T own_word = row0.at(G_A + A_F + link_opp(i), b ? xg * E : NOWHERE, g);
-          lf[k][i] = b ? own_word : lf[k][i];
-        }
-      }
-    }
-  }
+  if constexpr (!EARLY) load_f();
   __syncthreads();
 
   // ---- pass 4 ---------------------------------------------------------------------
