@@ -258,8 +258,8 @@ def adjoint_rollout(torch, n=512, steps=2000, checkpoint=100):
     drop_to_ellipse workload; FP32 storage, FP64 dL/dsigma.  Returns forward
     and backward (recompute + adjoint) times: the backward as the rollout runs
     it (the next segment recomputed on a second stream during the current
-    segment's adjoint steps)
-    and, for context, with both streams on every CU and on one stream."""
+    segment's adjoint steps) and, for context, with the overlap asked for and on
+    one stream."""
     from paper_2005_04642_amd import adjoint, workloads as Wk
     rn0, target, force, params = Wk.drop_to_ellipse(n)
     dev = "cuda:0"
@@ -296,7 +296,7 @@ def adjoint_rollout(torch, n=512, steps=2000, checkpoint=100):
            "ratio": round(fwd / bwd, 4), "loss": loss, "dL_dsigma": dsig}
     if checkpoint > 1:
         res["recompute_cus"] = adjoint.RECOMPUTE_CUS
-        # the same backward with both streams on every CU, and on one stream
+        # the same backward with the overlap asked for, and on one stream
         fwd2, bwd2, _, dsig2 = timed(True, 0)
         res["backward_s_two_streams_unconfined"] = round(bwd2, 3)
         fwd1, bwd1, _, dsig1 = timed(False)

@@ -255,10 +255,10 @@ int lbm_init_adjoint(lbm_handle* h, const void* rhoN0, const void* adj_pops0, vo
  * at a 256-byte aligned offset, lbm_batch_offsets) in two caller-owned buffers
  * of lbm_batch_pops_bytes() bytes.  Every lbm_batch_step is one launch of a
  * persistent-style kernel: each workgroup owns a bin of (lattice, tile) work
- * items, planned on the host so that the bins' costs (march iterations) are
- * balanced (longest processing time first).  The tile shape (workgroup width
- * and chunk height) comes from a table of candidates; lbm_batch_autotune times
- * them on the batch itself and keeps the fastest.  Each lattice evolves exactly
+ * items, planned on the host so that the largest bin's cost (in march
+ * iterations) is smallest.  The workgroup width and the cap on chunk heights
+ * come from a table of candidates; lbm_batch_autotune times them on the batch
+ * itself and keeps the fastest.  Each lattice evolves exactly
  * as it would alone under lbm_step. */
 typedef struct lbm_batch lbm_batch;
 
@@ -386,14 +386,13 @@ int64_t lbm_step_count(const lbm_handle* h);
 /* ---- sharing the GPU between two streams of work --------------------------
  * For callers that run independent work side by side on one GPU (the
  * checkpointed adjoint recomputes the next segment's states while it runs the
- * current segment's adjoint steps).  On small lattices a step keeps few CUs
- * busy for long (each tile's march starts with a fixed pipeline fill), so two
- * streams confined to disjoint sets of CUs overlap where two unconfined ones
- * would queue one kernel behind the other. */
+ * current segment's adjoint steps): two streams confined to disjoint sets of
+ * CUs run side by side where two unconfined ones may queue one kernel behind
+ * the other.  Plans for fewer CUs need more rounds of tiles: measure. */
 
 /* Plan the tiles of the forward step (lbm_step, lbm_fields) for ncu_step CUs
- * and those of the adjoint's first pass for ncu_adjoint CUs instead of the
- * whole device (0: the whole device; larger values are clamped to it).
+ * and those of the adjoint step for ncu_adjoint CUs instead of the whole
+ * device (0: the whole device; larger values are clamped to it).
  * Results do not depend on the plan (every site takes the same arithmetic).
  * Host-side only; applies to launches made after the call.  LBM_EINVAL for a
  * NULL handle or a negative count. */

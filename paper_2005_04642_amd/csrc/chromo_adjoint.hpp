@@ -19,6 +19,8 @@
 //   pass 4 (stencil): g = grad rho^N transposed, then the colour index;
 //   pass 5 (gather) : pre-collision populations from rho_C, f_i, j, and the
 //                     pull-streaming gather transposed (a push).
+// Passes 2 to 5 run in one kernel over tiles (chromo_adjtile.hpp) on most
+// lattices, as the separate kernels below on the others.
 // Every App. B stencil D is a sum of antisymmetric pair differences, so on a
 // periodic lattice its transpose is -D.  With a mask, a tap on a solid site
 // reads the centre value; for an adjoint field lambda that is zero at solid
