@@ -356,11 +356,12 @@ __global__ void __launch_bounds__(64 * NWV, 1)
       acc = {t.hi, acc.lo + t.lo};
     }
   }
-  acc = wave_sum2(acc);
+  acc = wave_sum2(acc, acc.hi);
   if (tx == 0) red[w] = acc;
   __syncthreads();
   if (w == NWV - 1) {
-    const Sum2 tot = wave_sum2(tx < NWV ? red[tx] : Sum2{0.0, 0.0});
+    const Sum2 part = tx < NWV ? red[tx] : Sum2{0.0, 0.0};
+    const Sum2 tot = wave_sum2(part, part.hi);
     if (tx == 0) *sigma_part(ws, g, strip, chunk) = tot;
   }
 

@@ -1065,8 +1065,11 @@ __device__ __forceinline__ void march_tile(const StepArgs<typename ST::math>& a,
 }
 
 // An FP64 sum carried in two doubles (the rounded sum and what its rounding
-// left out): rounded to one double at the end, a sum of FP64 terms is the same
-// for every order of the terms, hence for every cut of a lattice into tiles.
+// left out).  Each addition is off by some 2^-104 of its result, so that for
+// different orders of the terms (cuts of a lattice into tiles) the sums, rounded
+// to one double, differ only where they lie that close to a rounding boundary,
+// or cancel.  Past FP64's range the remainders are NaN and reach the sum: there
+// wave_sum2 takes the plain sum, an infinity or NaN as one FP64 sum would give.
 struct Sum2 {
   double hi, lo;
 };
@@ -1081,9 +1084,16 @@ __device__ __forceinline__ Sum2 add2(const Sum2& a, const Sum2& b) {
   s = two_sum(s.hi, s.lo + t.hi);
   return two_sum(s.hi, s.lo + t.lo);
 }
-__device__ __forceinline__ Sum2 wave_sum2(Sum2 v) {
+// Sum over the wave, the same in every lane.  plain: the lane's sum of the same
+// terms in one double (a check of the sum once at its end: one in every addition
+// cost 0.7 us per adjoint step, 2 to 4 % on small lattices).
+__device__ __forceinline__ Sum2 wave_sum2(Sum2 v, double plain) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = add2(v, {__shfl_xor(v.hi, off, 64), __shfl_xor(v.lo, off, 64)});
+  if (!isfinite(v.hi)) {
+    for (int off = 32; off > 0; off >>= 1) plain += __shfl_xor(plain, off, 64);
+    v = {plain, 0.0};
+  }
   return v;
 }
 
@@ -1103,14 +1113,19 @@ template <int NT, typename T>
 __device__ __forceinline__ void add_sigma_parts(const SigmaParts<T>& p) {
   __shared__ Sum2 red[NT / 64];
   Sum2 v = {0.0, 0.0};
-  for (int j = threadIdx.x; j < p.g.nstrips * p.g.nchunks; j += NT)
-    v = add2(v, *sigma_part(p.ws, p.g, j % p.g.nstrips, j / p.g.nstrips));
-  v = wave_sum2(v);
+  double plain = 0.0;
+  for (int j = threadIdx.x; j < p.g.nstrips * p.g.nchunks; j += NT) {
+    const Sum2 part = *sigma_part(p.ws, p.g, j % p.g.nstrips, j / p.g.nstrips);
+    v = add2(v, part);
+    plain += part.hi;
+  }
+  v = wave_sum2(v, plain);
   const int lane = threadIdx.x % 64;
   if (lane == 0) red[threadIdx.x / 64] = v;
   __syncthreads();
   if (threadIdx.x >= 64) return;
-  v = wave_sum2(lane < NT / 64 ? red[lane] : Sum2{0.0, 0.0});
+  v = lane < NT / 64 ? red[lane] : Sum2{0.0, 0.0};
+  v = wave_sum2(v, v.hi);
   if (lane == 0) *p.dsigma += v.hi;
 }
 
