@@ -147,25 +147,27 @@ void cut_columns(chromo::Geom& g, int txmax) {
 // They have to save a tenth of the march iterations: chunks of several rounds
 // share fewer rows in the caches (FP32 adjoint 4096^2, 170 iterations in two
 // rounds against 177 in one: 1.78 against 1.74 ms).
-chromo::Geom plan_march(const lbm_params& p, int ncu, int ntx) {
+chromo::Geom plan_march(const lbm_params& p, int ncu, int ntx, long long* march_iterations = nullptr) {
   chromo::Geom g = geom_of(p);
   cut_columns(g, ntx - 2 * halo(p));
   constexpr int FILL = chromo::Pipe<4>::IT0, MAX_ROUNDS = 8;
   auto iterations = [&](int nch, long long rounds) { return rounds * (FILL + (g.F + 4LL * nch - 1) / (4LL * nch)); };
   const int maxchunks = std::max(1, g.F / 4);
   int chunks = std::max(1, std::min(ncu / g.nstrips, maxchunks));
+  long long planned = iterations(chunks, std::max(1, (g.nstrips + ncu - 1) / ncu));
   if (g.nstrips <= ncu) {
-    long long best = iterations(chunks, 1) * 9 / 10;
+    long long best = planned * 9 / 10;
     for (int nch = chunks + 1; nch <= maxchunks; ++nch) {
       const long long rounds = ((long long)g.nstrips * nch + ncu - 1) / ncu;
       if (rounds > MAX_ROUNDS) break;
       if (iterations(nch, rounds) < best) {
-        best = iterations(nch, rounds);
+        best = planned = iterations(nch, rounds);
         chunks = nch;
       }
     }
   }
   cut_rows(g, chunks);
+  if (march_iterations) *march_iterations = planned;
   return g;
 }
 
@@ -190,13 +192,27 @@ chromo::Geom plan_tile(const lbm_params& p, int ncu, int rows, int h, int* round
 // gathers more halo rows, which costs more than the fill once the march's
 // chunks are tall.  Measured per step on 256 CUs, march against tile, periodic
 // lattices: FP32 64^2 16.0 / 6.8 us, 256^2 18.0 / 8.5, 512^2 22.1 / 14.5,
-// 724^2 (2 rounds) 30.4 / 26.7, 900^2 (3) 37.6 / 40.3; FP16 724^2 (2) 27.4 /
-// 21.9, 900^2 (3) 34.4 / 32.4, 1024^2 (4) 38.0 / 41.2; FP64 64^2 15.9 / 10.5,
+// 724^2 (2 rounds) 30.4 / 26.7, 900^2 (3) 37.6 / 40.3; FP64 64^2 15.9 / 10.5,
 // 512^2 (2) 39.3 / 29.4, 724^2 (4) 58.7 / 57.3, 900^2 (6) 84.0 / 85.9.  Two
 // region rows per wave where one round of the shorter tiles holds the lattice
 // (64^2 FP32: 6.8 us against 8.0 with three), else three (512^2: 14.5 against
 // 16.8); FP64 has registers for two, pass 1 in FP64 for four in each of 8
 // waves.
+//
+// Two lines need more than the rounds (march / tile, us per step):
+// - 16-bit words, three rounds: a short march keeps up with tall tiles.  Region
+//   rows of the rounds against march iterations, stencil 3333: 490 x 1400 117 /
+//   11 30.2 / 29.9, 518 x 1400 120 / 11 30.0 / 29.8, 856^2 120 / 11 30.1 / 30.5,
+//   518 x 1480 126 / 11 30.4 / 31.1, 518 x 1620 132 / 11 31.1 / 32.6, 880^2 126 /
+//   12 33.5 / 31.3; 1111 1288^2 138 / 15 37.2 / 36.5.  (In four, FP16 1024^2
+//   38.0 / 41.2.)
+// - FP64, four rounds, the smaller halos: past the 256 MB of the last cache the
+//   tiles' halo comes from memory.  Stencil 1111, both states' bytes: 1030^2
+//   walled 306 MB 75.3 / 73.3, 1060^2 walled 324 MB 82.6 / 82.5, periodic 81.9 /
+//   77.4, 1081^2 walled 337 MB 84.2 / 87.7, 1146^2 378 MB walled 94.0 / 97.6,
+//   1215^2 425 MB 101.8 / 107.4, walled 101.9 / 111.1; 3131 1020^2 300 MB 81.6 /
+//   74.7.
+constexpr double TILE_CACHED_BYTES = 320e6;
 chromo::Geom plan(const lbm_params& p, int ncu, bool adjoint = false) {
   const bool f64 = p.storage == LBM_STORAGE_F64;
   const int waves = chromo::tile_waves(f64, adjoint);
@@ -206,15 +222,18 @@ chromo::Geom plan(const lbm_params& p, int ncu, bool adjoint = false) {
     g.tile = slots;
     return g;
   };
+  long long iterations = 0;
+  const chromo::Geom march = plan_march(p, ncu, chromo::ntx_for(p.storage, adjoint), &iterations);
   chromo::Geom g = tiles(f64 && adjoint ? 4 : 2);
   if (f64) {
-    if (rounds <= 4) return g;
-  } else {
-    if (rounds == 1) return g;
-    g = tiles(3);
-    if (rounds <= (p.storage == LBM_STORAGE_F32 ? 2 : 3)) return g;
+    const double states = 2.0 * words_of(p.storage) * word_bytes_of(p.storage) * (double)p.nx * (double)p.ny;
+    return rounds <= (adjoint || states <= TILE_CACHED_BYTES ? 4 : 3) ? g : march;
   }
-  return plan_march(p, ncu, chromo::ntx_for(p.storage, adjoint));
+  if (rounds == 1) return g;
+  g = tiles(3);
+  if (rounds <= 2) return g;
+  const bool worth = (long long)rounds * (g.TY + 2 * halo(p)) <= 11 * iterations;
+  return rounds == 3 && p.storage != LBM_STORAGE_F32 && worth ? g : march;
 }
 
 // Launch plan of the adjoint's passes 2-5: one kernel over tiles
