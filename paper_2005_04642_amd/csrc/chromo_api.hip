@@ -772,6 +772,7 @@ size_t batch_items_cap(const lbm_params* p, int nsim) {
 
 struct BatchPlan {
   int ntx = 0, tycap = 0, nbins = 0;
+  int tiles = 0;                   // some lattice runs as tiles
   std::vector<chromo::Geom> geom;  // of every lattice
   std::vector<unsigned char> sims;
   std::vector<int> bin_start, items;
@@ -845,6 +846,7 @@ BatchPlan batch_plan(const lbm_params* p, int nsim, const std::vector<size_t>& o
   }
   b.max_cost = (double)best / BATCH_QUARTERS;
   b.sims.resize((size_t)nsim * ops.sim_desc_bytes);
+  for (const chromo::Geom& g : b.geom) b.tiles |= g.tile != 0;
   for (int k = 0; k < nsim; ++k)
     ops.sim_desc(p[k], b.geom[k], (unsigned long long)off[k], force[k], bnc[k],
                  &b.sims[(size_t)k * ops.sim_desc_bytes]);
@@ -918,9 +920,9 @@ int batch_upload(lbm_batch* b, BatchPlan&& pl, hipStream_t s) {
 
 int batch_step_impl(lbm_batch* b, int nsteps, hipStream_t s) {
   for (int k = 0; k < nsteps; ++k) {
-    hipError_t e = b->ops->batch(b->plan.ntx, b->p[0].stencil, b->p[0].walls_y, b->masked, b->pops[b->live],
-                                 b->pops[1 - b->live], b->d_sims,
-                                 b->d_bin_start, b->d_items, b->plan.nbins, s);
+    hipError_t e = b->ops->batch(b->plan.ntx, b->p[0].stencil, b->p[0].walls_y, b->masked, b->plan.tiles,
+                                 b->pops[b->live], b->pops[1 - b->live], b->d_sims, b->d_bin_start, b->d_items,
+                                 b->plan.nbins, s);
     if (e != hipSuccess) return fail(LBM_EHIP, "batch step launch: %s", hipGetErrorString(e));
     b->live = 1 - b->live;
     b->steps += 1;

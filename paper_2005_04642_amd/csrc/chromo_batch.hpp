@@ -32,13 +32,17 @@ struct BatchArgs {
 // shape, shared by the waves of the workgroup (12 with 4 rows each, or 8 with 6).
 constexpr int BATCH_TILE_ROWS = 48;
 
-template <typename ST, int NTX, int NR, int RG, int RK, int RP, int RU, bool WALLS = false, bool MASK = false>
+// TILES: some of the plan's items are tiles (FP32 arithmetic; double has no
+// registers for tiles of this height).  A plan of marches only takes the kernel
+// without them: beside the tile's code the march itself runs 3 to 5 % slower
+// (FP32, 1000 lattices of 64^2 at 128 columns 268 -> 257 us per step; 256 of
+// them at stencil 1111 57.8 -> 56.3).
+template <typename ST, int NTX, int NR, int RG, int RK, int RP, int RU, bool WALLS, bool MASK, bool TILES>
 __global__ void __launch_bounds__(NTX * NR, 1) chromo_batch_kernel(BatchArgs<typename ST::math> b) {
   using T = typename ST::math;
   using PP = Pipe<NR>;
   static_assert(NTX > 2 * (RG + RK + RU), "strip must be wider than its halo");
-  // (double has no registers for tiles of this height)
-  constexpr bool TILES = sizeof(T) == 4;
+  static_assert(!TILES || sizeof(T) == 4, "tile items need FP32 arithmetic");
   constexpr int NWV = NTX * NR / 64, NSLOT = BATCH_TILE_ROWS / NWV;
   constexpr Radii radii = {RG, RK, RP, RU};
   union Lds {
@@ -47,14 +51,17 @@ __global__ void __launch_bounds__(NTX * NR, 1) chromo_batch_kernel(BatchArgs<typ
   };
   __shared__ Lds lds;
   Smem<T, NTX, PP::RING>& sm = lds.march;
-  // The tables are never written while the kernel runs.  With FP32 arithmetic
-  // they are read through the constant address space: by scalar loads into
-  // scalar registers, as kernel arguments are, which also ends the spills of the
-  // 192-column kernel (9 VGPRs).  FP64 runs 4 % slower that way and copies them
-  // into registers.
+  // The tables are never written while the kernel runs.  Kernels with FP32
+  // arithmetic read them through the constant address space, by scalar loads
+  // into scalar registers, as kernel arguments are (us per step, copied into
+  // registers / that way: 48 periodic FP32 lattices of 64^2 to 512^2 138 / 120,
+  // 24 masked ones at stencil 1111 68.7 / 61.8, 1000 FP16 ones of 64^2 240 /
+  // 230), but for those that run slower so: walls (48 FP32 lattices 126 / 143),
+  // and FP32 words without tiles or masks (1000 of 64^2 257 / 266).  FP64 (397 /
+  // 416) copies them too.
   typedef const __attribute__((address_space(4))) int* ConstInts;
   typedef const __attribute__((address_space(4))) SimDesc<T>* ConstSims;
-  constexpr bool SCALAR = sizeof(T) == 4;
+  constexpr bool SCALAR = sizeof(T) == 4 && !WALLS && (TILES || MASK || is_ofs16<ST>::value);
   const int k0 = b.bin_start[blockIdx.x], k1 = b.bin_start[blockIdx.x + 1];
   for (int k = k0; k < k1; ++k) {
     int sim, tile;

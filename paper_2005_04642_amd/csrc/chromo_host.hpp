@@ -80,8 +80,9 @@ struct Ops {
   hipError_t (*solid_fields)(const lbm_params& p, const Geom& g, const void* src, const void* force,
                              const unsigned char* mask, void* ws, void* rho, void* ux, void* uy, void* rhoN,
                              hipStream_t s);
-  // batched periodic step: ntx in batch_ntx (0-terminated); tables in device memory
-  hipError_t (*batch)(int ntx, const int* radii, int walls, int masked, const void* src, void* dst,
+  // batched step: ntx in batch_ntx (0-terminated; walls or masks with FP32
+  // arithmetic: 128); tiles: some items are tiles; tables in device memory
+  hipError_t (*batch)(int ntx, const int* radii, int walls, int masked, int tiles, const void* src, void* dst,
                       const void* sims, const int* bin_start, const int* items, int nbins, hipStream_t s);
   // one SimDesc<math> of lattice p with tile plan g, byte offset off, force
   // field (device [2][ny][nx] or null) and mask bounce bits (or null), written to out

@@ -378,11 +378,18 @@ hipError_t init_adjoint(const lbm_params& p, const Geom& g0, const void* rhoN0, 
 }
 
 // ---------------------------------------------------------------------------
-// batched periodic step (chromo_batch_kernel)
+// batched step (chromo_batch_kernel)
 // ---------------------------------------------------------------------------
-template <typename S, int NTX, int RG, int RK, int RP, int RU, bool WALLS = false, bool MASK = false>
-hipError_t batch_launch(const BatchArgs<typename S::math>& b, int nbins, hipStream_t s) {
-  hipLaunchKernelGGL((chromo_batch_kernel<S, NTX, Shape<S>::nr, RG, RK, RP, RU, WALLS, MASK>), dim3(nbins),
+template <typename S, int NTX, int RG, int RK, int RP, int RU, bool WALLS, bool MASK>
+hipError_t batch_launch(const BatchArgs<typename S::math>& b, int tiles, int nbins, hipStream_t s) {
+  if constexpr (Shape<S>::f64) {
+    if (tiles) return hipErrorInvalidValue;
+  } else if (tiles) {
+    hipLaunchKernelGGL((chromo_batch_kernel<S, NTX, Shape<S>::nr, RG, RK, RP, RU, WALLS, MASK, true>), dim3(nbins),
+                       dim3(NTX * Shape<S>::nr), 0, s, b);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((chromo_batch_kernel<S, NTX, Shape<S>::nr, RG, RK, RP, RU, WALLS, MASK, false>), dim3(nbins),
                      dim3(NTX * Shape<S>::nr), 0, s, b);
   return hipGetLastError();
 }
@@ -390,22 +397,22 @@ hipError_t batch_launch(const BatchArgs<typename S::math>& b, int nbins, hipStre
 // batches of walled lattices, or with solid-site masks on some lattices
 // (MASK): built for the stencil profiles (3,3,3,3), (3,1,3,1) and (1,1,1,1)
 template <typename S, int NTX, bool WALLS, bool MASK>
-hipError_t batch_special(const BatchArgs<typename S::math>& b, const int* r, int nbins, hipStream_t s) {
+hipError_t batch_special(const BatchArgs<typename S::math>& b, const int* r, int tiles, int nbins, hipStream_t s) {
   if (r[0] == 3 && r[1] == 3 && r[2] == 3 && r[3] == 3)
-    return batch_launch<S, NTX, 3, 3, 3, 3, WALLS, MASK>(b, nbins, s);
+    return batch_launch<S, NTX, 3, 3, 3, 3, WALLS, MASK>(b, tiles, nbins, s);
   if (r[0] == 3 && r[1] == 1 && r[2] == 3 && r[3] == 1)
-    return batch_launch<S, NTX, 3, 1, 3, 1, WALLS, MASK>(b, nbins, s);
+    return batch_launch<S, NTX, 3, 1, 3, 1, WALLS, MASK>(b, tiles, nbins, s);
   if (r[0] == 1 && r[1] == 1 && r[2] == 1 && r[3] == 1)
-    return batch_launch<S, NTX, 1, 1, 1, 1, WALLS, MASK>(b, nbins, s);
+    return batch_launch<S, NTX, 1, 1, 1, 1, WALLS, MASK>(b, tiles, nbins, s);
   return hipErrorNotSupported;
 }
 
 template <typename S, int NTX>
-hipError_t batch_radii(const BatchArgs<typename S::math>& b, const int* r, int nbins, hipStream_t s) {
+hipError_t batch_radii(const BatchArgs<typename S::math>& b, const int* r, int tiles, int nbins, hipStream_t s) {
   const int code = (r[0] == 3) * 8 + (r[1] == 3) * 4 + (r[2] == 3) * 2 + (r[3] == 3);
 #define CHROMO_CASE(C, A, B, P, U) \
   case C:                          \
-    return batch_launch<S, NTX, A, B, P, U>(b, nbins, s);
+    return batch_launch<S, NTX, A, B, P, U, false, false>(b, tiles, nbins, s);
   switch (code) {
     CHROMO_CASE(0, 1, 1, 1, 1)
     CHROMO_CASE(1, 1, 1, 1, 3)
@@ -429,16 +436,19 @@ hipError_t batch_radii(const BatchArgs<typename S::math>& b, const int* r, int n
 }
 
 template <typename S, int NTX>
-hipError_t batch_kind(const BatchArgs<typename S::math>& b, const int* r, int walls, int masked, int nbins,
+hipError_t batch_kind(const BatchArgs<typename S::math>& b, const int* r, int walls, int masked, int tiles, int nbins,
                       hipStream_t s) {
-  if (walls) return batch_special<S, NTX, true, false>(b, r, nbins, s);
-  if (masked) return batch_special<S, NTX, false, true>(b, r, nbins, s);
-  return batch_radii<S, NTX>(b, r, nbins, s);
+  if constexpr (Shape<S>::f64 || NTX == 128) {
+    if (walls) return batch_special<S, NTX, true, false>(b, r, tiles, nbins, s);
+    if (masked) return batch_special<S, NTX, false, true>(b, r, tiles, nbins, s);
+  }
+  if (walls || masked) return hipErrorInvalidValue;
+  return batch_radii<S, NTX>(b, r, tiles, nbins, s);
 }
 
 template <typename S>
-hipError_t batch(int ntx, const int* radii, int walls, int masked, const void* src, void* dst, const void* sims,
-                 const int* bin_start, const int* items, int nbins, hipStream_t s) {
+hipError_t batch(int ntx, const int* radii, int walls, int masked, int tiles, const void* src, void* dst,
+                 const void* sims, const int* bin_start, const int* items, int nbins, hipStream_t s) {
   using T = typename S::math;
   BatchArgs<T> b;
   b.src = static_cast<const char*>(src);
@@ -447,10 +457,10 @@ hipError_t batch(int ntx, const int* radii, int walls, int masked, const void* s
   b.bin_start = bin_start;
   b.items = items;
   if constexpr (Shape<S>::f64) {
-    if (ntx == NTX_F64) return batch_kind<S, NTX_F64>(b, radii, walls, masked, nbins, s);
+    if (ntx == NTX_F64) return batch_kind<S, NTX_F64>(b, radii, walls, masked, tiles, nbins, s);
   } else {
-    if (ntx == 128) return batch_kind<S, 128>(b, radii, walls, masked, nbins, s);
-    if (ntx == 192) return batch_kind<S, 192>(b, radii, walls, masked, nbins, s);
+    if (ntx == 128) return batch_kind<S, 128>(b, radii, walls, masked, tiles, nbins, s);
+    if (ntx == 192) return batch_kind<S, 192>(b, radii, walls, masked, tiles, nbins, s);
   }
   return hipErrorInvalidValue;
 }
