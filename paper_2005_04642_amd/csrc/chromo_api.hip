@@ -245,11 +245,12 @@ chromo::Geom plan(const lbm_params& p, int ncu, bool adjoint = false) {
 // masked 64^2 35.7 / 22.7, 512^2 60.6 / 46.8 (3), 4096^2 2691 / 2600; FP64
 // periodic 64^2 27.6 / 26.5, 512^2 83.5 / 73.7 (6), 1448^2 675 / 592; walls
 // 512^2 147 / 133 (3); masked 64^2 43.4 / 34.4 and, past one round, 512^2 103
-// against 109 to 117: there the separate passes stay (counted for 256 CUs
-// whatever the budget, as dL/dsigma's last bit may differ between the two).
+// against 109 to 117: there the separate passes stay (counted for the whole
+// device, ncu_device, whatever the budget ncu, as dL/dsigma's last bit may differ
+// between the two).
 // They also run lattices of fewer than 4 fluid rows between walls, whose mirror
 // images overlap, and workspace rows beyond 31-bit offsets.
-chromo::Geom plan_tail(const lbm_params& p, int ncu, bool masked) {
+chromo::Geom plan_tail(const lbm_params& p, int ncu, int ncu_device, bool masked) {
   const chromo::Geom none = geom_of(p);
   const bool f64 = p.storage == LBM_STORAGE_F64;
   if (none.walls && none.F < 4) return none;
@@ -266,7 +267,7 @@ chromo::Geom plan_tail(const lbm_params& p, int ncu, bool masked) {
   chromo::Geom g = tiles(2);
   if (f64 && masked) {
     int whole = 0;
-    plan_tile(p, 256, chromo::tail_waves(f64, 2) * 2, h, &whole);
+    plan_tile(p, ncu_device, chromo::tail_waves(f64, 2) * 2, h, &whole);
     return whole > 1 ? none : g;
   }
   if (rounds > 1) {
@@ -325,6 +326,7 @@ struct lbm_handle {
   chromo::Geom g;      // forward step kernel
   chromo::Geom g_adj;  // adjoint pass 1 (workgroup shape ntx_for(storage, true))
   int ncu_adj;         // CUs its passes 2-5 are planned for (plan_tail)
+  int ncu;             // CUs of the device
   const chromo::Ops* ops;
   double* scratch = nullptr;             // this device's static scratch (lbm_step_static)
   const unsigned char* solid = nullptr;  // device mask of solid sites (lbm_set_solid), or null
@@ -421,7 +423,7 @@ int lbm_init(const lbm_params* p, const void* rhoN0, const void* force, void* po
   h->steps = 0;
   h->g = plan(*p, ncu > 0 ? ncu : 1);
   h->g_adj = plan(*p, ncu > 0 ? ncu : 1, true);
-  h->ncu_adj = ncu > 0 ? ncu : 1;
+  h->ncu_adj = h->ncu = ncu > 0 ? ncu : 1;
   h->ops = ops_of(p->storage);
   h->scratch = scr;
 
@@ -582,7 +584,7 @@ int lbm_adjoint_step(lbm_handle* h, const void* pops_t, const void* adj_next, vo
   int st = adjoint_args(h, adj_next, adj_out, workspace, ws_bytes);
   if (st != LBM_OK) return st;
   if (!pops_t) return fail(LBM_EINVAL, "pops_t must be non-NULL");
-  const chromo::Geom gt = plan_tail(h->p, h->ncu_adj, h->solid != nullptr);
+  const chromo::Geom gt = plan_tail(h->p, h->ncu_adj, h->ncu, h->solid != nullptr);
   hipError_t e = h->ops->adjoint(h->p, h->g_adj, gt, false, true, pops_t, h->force, adj_next, adj_out, workspace, dL_dsigma_dev,
                                  dL_dforce_dev, h->solid, bounce_bits(h), stream);
   if (e != hipSuccess) return fail(LBM_EHIP, "adjoint launch: %s", hipGetErrorString(e));
@@ -599,7 +601,7 @@ int lbm_adjoint_steps(lbm_handle* h, int32_t nsteps, const void* const* states, 
   if (nsteps > 0 && !states) return fail(LBM_EINVAL, "states must be non-NULL");
   for (int j = 0; j < nsteps; ++j)
     if (!states[j]) return fail(LBM_EINVAL, "states[%d] is NULL", j);
-  const chromo::Geom gt = plan_tail(h->p, h->ncu_adj, h->solid != nullptr);
+  const chromo::Geom gt = plan_tail(h->p, h->ncu_adj, h->ncu, h->solid != nullptr);
   for (int k = 0; k < nsteps; ++k) {
     const void* in = (k & 1) ? adj_b : adj_a;
     void* out = (k & 1) ? adj_a : adj_b;
@@ -1083,7 +1085,7 @@ int lbm_batch_init(const lbm_params* p, int nsim, const void* const* rhoN0, void
     h.steps = 0;
     h.g = plan(p[k], ncu);
     h.g_adj = plan(p[k], ncu, true);
-    h.ncu_adj = ncu;
+    h.ncu_adj = h.ncu = ncu;
     h.ops = b->ops;
     hipError_t e = b->ops->init(p[k], h.g, rhoN0[k], h.pops[0], stream);
     if (e != hipSuccess) {

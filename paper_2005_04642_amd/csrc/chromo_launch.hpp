@@ -120,12 +120,12 @@ template <typename S, int MODE, bool MASK = false>
 hipError_t tile_launch(const StepArgs<typename S::math>& a, const int* r, hipStream_t s) {
   if constexpr (Shape<S>::f64 && MODE == MODE_ADJ) {
     if (a.g.tile == 4) return tile_shape<S, 4, MODE, MASK>(a, r, s);
-    return hipErrorInvalidValue;
+  } else {
+    if constexpr (!Shape<S>::f64) {
+      if (a.g.tile == 3) return tile_shape<S, 3, MODE, MASK>(a, r, s);
+    }
+    if (a.g.tile == 2) return tile_shape<S, 2, MODE, MASK>(a, r, s);
   }
-  if constexpr (!Shape<S>::f64) {
-    if (a.g.tile == 3) return tile_shape<S, 3, MODE, MASK>(a, r, s);
-  }
-  if (a.g.tile == 2) return tile_shape<S, 2, MODE, MASK>(a, r, s);
   return hipErrorInvalidValue;
 }
 
