@@ -269,7 +269,8 @@ size_t lbm_batch_pops_bytes(const lbm_params* p, int nsim);
 /* Byte offset of every lattice's buffer inside a packed buffer (offsets[nsim]). */
 int lbm_batch_offsets(const lbm_params* p, int nsim, size_t* offsets);
 
-/* Bytes of device workspace of a batch (work-list tables, mass partials). */
+/* Bytes of device workspace of a batch (work-list tables, mass partials): room
+ * for the plan of most items, chunks of 8 rows (8 bytes per item). */
 size_t lbm_batch_workspace_bytes(const lbm_params* p, int nsim);
 
 /* Create a batch and write every lattice's rest state (as lbm_init) into

@@ -5,8 +5,9 @@
 // chain of transposed stencils and the push).  As in the step's tile kernel
 // (chromo_tile.hpp), the region is 64 columns wide, one wavefront per row, and
 // wave w takes rows w, w + NWV, ... in every phase: what a site hands from one
-// pass to the next stays in its thread's registers, the stencils' operands go
-// through LDS, and every plane that passes 2-4 read is fetched up front, each
+// pass to the next stays in its thread's registers (FP64 in 16 waves spills 6 of
+// 128 VGPRs between walls and 4 with a mask), the stencils' operands go through
+// LDS, and every plane that passes 2-4 read is fetched up front, each
 // only where it is used (lanes elsewhere hold an offset beyond the row's buffer
 // resource, which fetches nothing).  The passes' intermediate planes (7 + 2 + 2
 // per site, written once and read up to 24 times through the cache by the
@@ -24,8 +25,9 @@
 // arithmetic and LDS reads, half of them on halo sites (512^2: 26.5 -> 20 us);
 // on large lattices the planes' traffic, 28 of them read with the halo and 18
 // written (4096^2: 1.18 -> 1.08 ms).  16 waves of 2 or 3 rows while one round
-// of workgroups holds the lattice, 8 waves of 6 rows beyond: two of those share
-// a CU, one's loads under the other's arithmetic.
+// of workgroups holds the lattice, 8 waves of 6 rows beyond: in FP32 two of those
+// (74 KB of LDS each; FP64 148 KB) share a CU, one's loads under the other's
+// arithmetic.
 #pragma once
 
 #include "chromo_adjoint.hpp"

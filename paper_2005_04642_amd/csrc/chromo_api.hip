@@ -174,7 +174,9 @@ chromo::Geom plan_march(const lbm_params& p, int ncu, int ntx, long long* march_
 // Tiles of at most 64 - 2 h columns and `rows` - 2 h rows (regions of 64
 // columns and `rows` rows), one workgroup per CU at a time: as many equal
 // chunks as fill the rounds of workgroups that the tallest tiles need, none
-// below 4 rows (64^2 FP32: 6.8 us per step at 4 rows, 8.3 at 14, 6.7 at 2).
+// below 4 rows (64^2 FP32: 6.8 us per step at 4 rows, 8.3 at 14, 6.7 at 2; in
+// several rounds, filled against tallest: FP16 490 x 1400 29.9 / 34.0, FP64 1111
+// 1100^2 84.6 / 92.5).
 chromo::Geom plan_tile(const lbm_params& p, int ncu, int rows, int h, int* rounds) {
   chromo::Geom g = geom_of(p);
   cut_columns(g, 64 - 2 * h);
@@ -258,8 +260,9 @@ chromo::Geom plan_tail(const lbm_params& p, int ncu, int ncu_device, bool masked
   const int h = chromo::adj::tail_halo({p.stencil[0], p.stencil[1], p.stencil[2], p.stencil[3]});
   int rounds = 0;
   auto tiles = [&](int slots) {
-    // (8-wave workgroups run two to a CU, but chunks cut for twice the CUs gather
-    // more halo: FP64 512^2 90 us against 74)
+    // (FP32's 8-wave workgroups run two to a CU, but cutting the chunks for twice
+    // the CUs changes nothing: 719^2 61 us, 1020^2 131, 2052^2 483 either way; FP64's
+    // take a CU each, and more chunks only gather more halo: 512^2 90 us against 74)
     chromo::Geom g = plan_tile(p, ncu, chromo::tail_waves(f64, slots) * slots, h, &rounds);
     g.tile = slots;
     return g;
@@ -740,9 +743,10 @@ chromo::Geom batch_geom_tiles(const lbm_params& p, int tycap) {
 }
 
 // Cost of an item of `rows` rows in quarters of a march iteration (0.85 to 1.1
-// us at 192 columns): a march is its fill and its rows, a tile its phases, the
-// wait for the stores of the tile before it, and its rows (8 us at 8 rows, 13 at
-// 16 alone in its bin, 20 as one of three).
+// us at 192 columns; the same weights serve 128): a march is its fill and its
+// rows, a tile its phases, the wait for the stores of the tile before it, and its
+// rows (8 us at 8 rows, 13 at 16 alone in its bin, 20 as one of three).  Masks do
+// not count.
 constexpr int BATCH_QUARTERS = 4;
 int batch_cost(const chromo::Geom& g, int rows, int nr, int it0) {
   return g.tile ? 8 + rows : BATCH_QUARTERS * (it0 + (rows + nr - 1) / nr);
@@ -948,10 +952,11 @@ struct lbm_batch {
 namespace {
 
 // Strip widths the batch kernels of this batch may use.  With FP32 arithmetic
-// the 192-wide strips (768 threads, at most 168 VGPRs) leave the walled and
-// masked variants few registers (162 VGPRs for walls at stencil 3333; masks
-// there spill 5), so walled and masked batches use 128-wide strips only.
-// Returns the count written to out.
+// walled and masked batches use 128-wide strips only: 192-wide ones (768 threads,
+// at most 168 VGPRs) spill 9 VGPRs with walls and 5 with masks at stencil 3333.
+// Walls, 128 / 192 columns, us per step: 1000 lattices of 64^2 262 / 295, 6 of
+// 64^2 to 512^2 22.6 / 25.7, 48 of them 127 / 126, 2 of 2048^2 313 / 341, 12 of
+// 1024^2 484 / 463, 20 of 511^2 232 / 205.  Returns the count written to out.
 int batch_widths(const lbm_batch* b, int* out) {
   int n = 0;
   for (int i = 0; i < 3 && b->ops->batch_ntx[i]; ++i) {

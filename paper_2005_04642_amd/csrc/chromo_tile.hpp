@@ -5,7 +5,8 @@
 // tile with H = r_g + r_K + r_u more columns and rows on every side.  The
 // region is 64 columns wide, one wavefront per row, and wave w takes rows w,
 // w + 16, ... of it (NSLOT of them), the same rows in every phase, so that all
-// a site hands from one phase to the next stays in its thread's registers;
+// a site hands from one phase to the next stays in its thread's registers (FP64
+// spills 4 of 128 VGPRs between walls and 2 with a mask, pass 1 there 4 of 256);
 // only the six stencil operands go through LDS.  Four phases, three barriers:
 //   gather of the whole region, colour densities, rho^N, Phi' (all rows' words
 //     in flight at once in the step);
